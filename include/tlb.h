@@ -233,8 +233,7 @@ tlb_status tlb_set_check_every(tlb_sim* sim, int64_t every);
 
 /*
  * Replay the steps of tlb_step from a captured hipGraph in chains of
- * steps_per_graph launches (an even number; 0, the default, launches every step
- * directly).  For small lattices, where a step takes about as long as its
+ * steps_per_graph steps (an even number; 0, the default, launches directly).  For small lattices, where a step takes about as long as its
  * launch, this removes most of the launch overhead.  The chain is captured on
  * the simulation's stream at the first tlb_step that needs it and replayed
  * after that; tlb_set_launch and tlb_set_kappa drop it (the launches hold the
@@ -401,7 +400,10 @@ tlb_status tlb_set_wetting_dev(tlb_sim* sim, int wall, const void* h_dev);
  * Launch shape of the fused step kernel.
  *   D2Q9: each workgroup sweeps a strip of `width` columns (64, 128 or 256)
  *     over `chunk` rows; variant 1 prefetches the next row's populations while
- *     the current row is collided, variant 0 does not.
+ *     the current row is collided, variant 0 does not.  Until a shape is set with
+ *     tlb_set_launch, tlb_step advances three- and four-component lattices of at
+ *     most 4 GiB two steps per launch, in a shape of its own, with bitwise the
+ *     same results; a shape set here is used for every step.
  *   D3Q19: each workgroup sweeps a tile of width x height columns (32x8 or
  *     64x4) over `chunk` planes; variant 1 keeps the next plane's populations in registers
  *     between their two uses, variant 0 reads them a second time from cache;

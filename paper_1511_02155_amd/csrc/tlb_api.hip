@@ -47,6 +47,7 @@ struct tlb_sim {
     bool ready;
     int64_t check_every;
     tlb_launch launch;
+    bool launch_set;          // the launch shape is the caller's: every step runs in exactly that shape
     double* hhost;            // [2][nc][nx*nz] h_m as last set from the host (range report)
     int64_t wet_outside[2];   // per wall: values with |4 h_m / (alpha kappa_m)| > 1, -1 if set from device memory
     bool wet_warned;
@@ -571,17 +572,38 @@ static hipError_t launch_one(const tlb_sim* s, const StepArgs<T>& a)
                                   s->p.collision == TLB_MRT, s->nc, s->stream);
 }
 
-// n steps, each launched directly.
+// Whether steps run two to a launch (tlb_pair2d.hip): D2Q9 of three or four components in the default
+// launch, a state of one buffer descriptor.
+static bool pair_steps(const tlb_sim* s)
+{
+    return s->p.lattice == TLB_D2Q9 && s->nc <= 4 && !s->launch_set && tlb_state_bytes(s) <= (int64_t)0xFFFFFF00;
+}
+
+// n steps launched directly, two to a launch where that is possible.  even: in an even number of
+// launches (n is even), so that the state ends in the buffer it started from.
 template <typename T>
-static tlb_status launch_steps(tlb_sim* s, int64_t n)
+static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
 {
     StepArgs<T> a = step_args<T>(s);
-    for (int64_t t = 0; t < n; ++t) {
-        a.src = (const T*)s->state[s->cur];
-        a.dst = (T*)s->state[s->cur ^ 1];
-        a.flip = s->cur;  // every other step sweeps each chunk the other way
-        HIPCHK(launch_one<T>(s, a));
+    int64_t pairs = pair_steps(s) ? n / 2 : 0;
+    if (even && (pairs & 1)) --pairs;
+    auto turn = [&](StepArgs<T>& x) {
+        x.src = (const T*)s->state[s->cur];
+        x.dst = (T*)s->state[s->cur ^ 1];
+        x.flip = s->cur;  // every other launch sweeps each chunk the other way
         s->cur ^= 1;
+    };
+    if (pairs > 0) {
+        StepArgs<T> b = a;
+        pair2d_shape<T>(b, s->nc, s->cus);
+        for (int64_t t = 0; t < pairs; ++t) {
+            turn(b);
+            HIPCHK(launch_pair2d<T>(b, s->p.collision == TLB_MRT, s->nc, s->stream));
+        }
+    }
+    for (int64_t t = 2 * pairs; t < n; ++t) {
+        turn(a);
+        HIPCHK(launch_one<T>(s, a));
     }
     return TLB_OK;
 }
@@ -601,7 +623,7 @@ static tlb_status run_steps(tlb_sim* s, int64_t n)
         if (!s->graph_exec) {
             drop_graph(s);  // a graph left by a failed instantiation
             HIPCHK(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
-            tlb_status st = launch_steps<T>(s, G);  // recorded, not run: cur is back at 0
+            tlb_status st = launch_steps<T>(s, G, true);  // recorded, not run: cur is back at 0
             hipGraph_t g = nullptr;
             const hipError_t e = hipStreamEndCapture(s->stream, &g);
             if (st) {
@@ -693,11 +715,12 @@ extern "C" tlb_status tlb_set_launch(tlb_sim* s, const tlb_launch* l)
         s->launch = d;
     }
     if (!launch_valid(s, &v)) return TLB_EINVAL;
-    if (memcmp(&v, &s->launch, sizeof(v)) != 0) {
+    if (!s->launch_set || memcmp(&v, &s->launch, sizeof(v)) != 0) {
         HIPCHK(hipStreamSynchronize(s->stream));
         drop_graph(s);  // the captured launches have the old shape
     }
     s->launch = v;
+    s->launch_set = true;
     return TLB_OK;
 }
 

@@ -21,6 +21,7 @@ struct StepArgs {
     int nchunks;  // chunks along the sweep axis
     int ntx, nty; // strips (D2Q9: ntx) / tiles (D3Q19: ntx * nty) across the sweep
     int nitems;   // ntx * nty * nchunks
+    int cols;     // D2Q9 two-step launches: columns of a strip
     int flip;     // D2Q9 strips: 1 reverses the sweep direction of every chunk (alternates per step)
     Phys<acc_t<T>> P;
     Phys<float> Pf;  // the same parameters for kernels whose arithmetic is FP32
@@ -38,6 +39,11 @@ __device__ __forceinline__ int xcd_item(int b, int G)
 
 template <typename T>
 hipError_t launch_step2d(const StepArgs<T>& a, int width, int hold, bool mrt, int nc, hipStream_t s);
+// Two D2Q9 steps in one launch (tlb_pair2d.hip), and its strips and chunks for the lattice of `a`.
+template <typename T>
+void pair2d_shape(StepArgs<T>& a, int nc, int cus);
+template <typename T>
+hipError_t launch_pair2d(const StepArgs<T>& a, bool mrt, int nc, hipStream_t s);
 template <typename T>
 hipError_t launch_step3d(const StepArgs<T>& a, int width, int height, int variant, bool mrt, int nc, hipStream_t s);
 template <typename T>

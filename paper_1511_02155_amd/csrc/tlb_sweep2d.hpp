@@ -129,6 +129,7 @@ __device__ __forceinline__ T pull2d_one(const StepArgs<T>& A, int j, int x, int 
 template <typename C>
 __device__ __forceinline__ void stencil9(C ac, C aS, C aD, C bc, C bS, C bD, C cc, C cS, C cD, int dir, C* g, C& lap)
 {
+#pragma clang fp contract(on)
     const C up = dir > 0 ? cc : ac, dn = dir > 0 ? ac : cc;
     const C Sup = dir > 0 ? cS : aS, Sdn = dir > 0 ? aS : cS;
     g[0] = bD * C(1.0 / 3.0) + (aD + cD) * C(1.0 / 12.0);
