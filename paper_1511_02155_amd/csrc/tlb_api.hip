@@ -234,25 +234,34 @@ static void default_launch(tlb_sim* s)
         s->launch.variant = (s->nc == 4 || (f64 && s->nc == 3)) ? 1 : 0;
         s->adj_launch = default_adj_launch(p, s->cus);
     } else {
-        // Measured on MI355X (256^3 FP32): 64x4 tiles holding the next plane,
-        // ~1000 wavefronts in flight; with FP32 storage the pipelined sweep
-        // (loads of plane z+2 in flight during the collision of plane z) is
-        // 5% faster.
-        // 32 x 8 tiles where 64-wide ones would leave lanes idle (96^3 FP32: 124 us per step against
-        // 175); chunks down to one plane for lattices too small to fill the chip (32^3: 12.7 us against
-        // 23.7 with four planes).
-        const int waste64 = (p.nx + 63) / 64 * 64 - p.nx, waste32 = (p.nx + 31) / 32 * 32 - p.nx;
-        int bx = (p.nx >= 64 && waste64 <= waste32) ? 64 : 32, by = bx == 64 ? 4 : 8;
-        const int ntx = (p.nx + bx - 1) / bx, nty = (p.ny + by - 1) / by;
-        const int64_t waves_per_item = (bx * by) / 64;
-        int64_t want_items = 1024 / waves_per_item;
-        int64_t nch = (want_items + (int64_t)ntx * nty - 1) / ((int64_t)ntx * nty);
-        if (nch < 1) nch = 1;
-        int chunk = (int)((p.nz + nch - 1) / nch);
-        if (chunk < 1) chunk = 1;
-        s->launch.width = bx;
-        s->launch.height = by;
-        s->launch.chunk = chunk;
+        // The default variants hold one workgroup per compute unit, so the chip runs `slots` items at
+        // once, and an item's time goes with its planes and the two it starts from (about three planes'
+        // worth).  The shape is the one with the smallest rounds * (chunk + 3): a few items more than
+        // the chip holds cost a second, nearly empty round (96^3 FP32: 288 items 176 us per step, 252
+        // items 116 us; 160^3 with several relaxation times: 300 items 774 us, 240 items 481 us).  A
+        // plane of a 32 x 8 tile takes 1.1 to 1.25 times a 64 x 4 tile's (its rows are shorter runs of
+        // memory), so the narrow tile is for lattices that leave wide ones idle; and several rounds
+        // cost about 1.2 times their planes (200^3: 200 items of all planes 1224 us, 1000 of 40 planes
+        // 1361 us), the starts of the later ones among them.
+        const int slots = s->cus > 0 ? s->cus : 256;
+        double best = 1e300;
+        for (int bx : {64, 32}) {
+            const int by = 256 / bx;
+            const int64_t tiles = (int64_t)((p.nx + bx - 1) / bx) * ((p.ny + by - 1) / by);
+            for (int64_t rounds = 1; rounds <= 64; ++rounds) {
+                const int64_t nch = std::min<int64_t>(p.nz, std::max<int64_t>(1, rounds * slots / tiles));
+                const int chunk = (int)((p.nz + nch - 1) / nch);
+                const int64_t items = tiles * ((p.nz + chunk - 1) / chunk);
+                const int64_t turns = (items + slots - 1) / slots;
+                const double cost = (double)turns * (chunk + 3) * (bx == 32 ? 1.2 : 1.0) * (turns > 1 ? 1.2 : 1.0);
+                if (cost < best) {
+                    best = cost;
+                    s->launch.width = bx;
+                    s->launch.height = by;
+                    s->launch.chunk = chunk;
+                }
+            }
+        }
         // the pipelined sweep is built for FP32 storage of three or four components (four: 2.11
         // against 2.34 ms with variant 1 at 256^3).  With five FP32 keeps plane z's populations
         // (variant 1: 3.09 against 3.31 ms); in FP64 those would spill, so it pulls plane z twice
