@@ -38,7 +38,7 @@ struct tlb_sim {
     int64_t seg_cap;
     hipStream_t aux;    // recomputes the next segment while the current one is reversed
     hipEvent_t seg_ready[2], main_mark;
-    void* fields;       // [11][N] (lazy)
+    void* fields;       // [nc + 8][N] (lazy, chemical potentials only)
     double* staging;    // device doubles for host I/O (lazy)
     size_t staging_elems;
     double* diag_partial;
@@ -781,12 +781,12 @@ extern "C" double tlb_bytes_per_node(const tlb_sim* s)
 template <typename T, typename TOut>
 static tlb_status field_impl(tlb_sim* s, int which, TOut* out)
 {
-    tlb_status st = ensure_fields(s);
-    if (st) return st;
-    const AuxGeom g = geom(s);
-    HIPCHK(launch_fields<T>(g, make_phys<acc_t<T>>(s->p), (const T*)s->state[s->cur], (const T*)s->wet, (T*)s->fields,
-                            s->stream));
-    HIPCHK(launch_export_field<T, TOut>(g, (const T*)s->fields, which, out, s->stream));
+    if (field_needs_all(s->nc, which)) {
+        tlb_status st = ensure_fields(s);
+        if (st) return st;
+    }
+    HIPCHK(launch_field<T, TOut>(geom(s), make_phys<acc_t<T>>(s->p), (const T*)s->state[s->cur], (const T*)s->wet,
+                                 (T*)s->fields, which, out, s->stream));
     return TLB_OK;
 }
 

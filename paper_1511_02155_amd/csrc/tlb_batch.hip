@@ -907,17 +907,17 @@ extern "C" tlb_status tlb_batch_get_field(tlb_batch* b, int32_t dom, int which, 
     const AuxGeom g = dom_geom(b, dom);
     tlb_status st = staging(b);
     if (st) return st;
-    if (!b->fields) BHIP(hipMalloc(&b->fields, (size_t)TLB_NFIELDS * b->max_nodes * b->esize));
+    if (field_needs_all(3, which) && !b->fields)
+        BHIP(hipMalloc(&b->fields, (size_t)TLB_NFIELDS * b->max_nodes * b->esize));
     if (b->prec == TLB_F32) {
         const float* wet = b->wet_off[dom] >= 0 ? (const float*)b->wet + b->wet_off[dom] : nullptr;
-        BHIP(launch_fields<float>(g, phys_of<acc_t<float>>(b->p[dom]), (const float*)b->state[b->cur] + b->off[dom], wet,
-                                  (float*)b->fields, b->stream));
-        BHIP(launch_export_field<float, double>(g, (const float*)b->fields, which, b->staging, b->stream));
+        BHIP(launch_field<float, double>(g, phys_of<acc_t<float>>(b->p[dom]), (const float*)b->state[b->cur] + b->off[dom],
+                                         wet, (float*)b->fields, which, b->staging, b->stream));
     } else {
         const double* wet = b->wet_off[dom] >= 0 ? (const double*)b->wet + b->wet_off[dom] : nullptr;
-        BHIP(launch_fields<double>(g, phys_of<acc_t<double>>(b->p[dom]), (const double*)b->state[b->cur] + b->off[dom], wet,
-                                   (double*)b->fields, b->stream));
-        BHIP(launch_export_field<double, double>(g, (const double*)b->fields, which, b->staging, b->stream));
+        BHIP(launch_field<double, double>(g, phys_of<acc_t<double>>(b->p[dom]),
+                                          (const double*)b->state[b->cur] + b->off[dom], wet, (double*)b->fields, which,
+                                          b->staging, b->stream));
     }
     BHIP(hipMemcpyAsync(out, b->staging, sizeof(double) * g.N, hipMemcpyDeviceToHost, b->stream));
     BHIP(hipStreamSynchronize(b->stream));

@@ -76,11 +76,12 @@ constexpr int diag_slots(int nc) { return 2 * nc + 5; }
 template <typename T, typename TIn>
 hipError_t launch_init(const AuxGeom& g, const Phys<acc_t<T>>& P, const TIn* C, const TIn* u, const T* wet,
                        T* state, hipStream_t s);
-template <typename T>
-hipError_t launch_fields(const AuxGeom& g, const Phys<acc_t<T>>& P, const T* state, const T* wet,
-                         T* fields /*[11][N] deviations*/, hipStream_t s);
+// One field into out[N].  F: [nc + 8][N] scratch, used only where field_needs_all() (the chemical
+// potentials, whose stencils read the concentrations of the neighbours).
+bool field_needs_all(int nc, int which);
 template <typename T, typename TOut>
-hipError_t launch_export_field(const AuxGeom& g, const T* fields, int which, TOut* out, hipStream_t s);
+hipError_t launch_field(const AuxGeom& g, const Phys<acc_t<T>>& P, const T* state, const T* wet, T* F, int which,
+                        TOut* out, hipStream_t s);
 template <typename T, typename TOut>
 hipError_t launch_get_pops(const AuxGeom& g, const T* state, int species, TOut* out, hipStream_t s);
 template <typename T, typename TIn>
