@@ -594,7 +594,9 @@ template <typename T>
 static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
 {
     StepArgs<T> a = step_args<T>(s);
-    int64_t pairs = pair_steps(s) ? n / 2 : 0;
+    StepArgs<T> b = a;
+    int64_t pairs = n / 2;
+    if (pairs > 0 && !(pair_steps(s) && pair2d_shape<T>(b, s->nc, s->cus, s->launch.chunk, s->launch.width))) pairs = 0;
     if (even && (pairs & 1)) --pairs;
     auto turn = [&](StepArgs<T>& x) {
         x.src = (const T*)s->state[s->cur];
@@ -602,13 +604,9 @@ static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
         x.flip = s->cur;  // every other launch sweeps each chunk the other way
         s->cur ^= 1;
     };
-    if (pairs > 0) {
-        StepArgs<T> b = a;
-        pair2d_shape<T>(b, s->nc, s->cus);
-        for (int64_t t = 0; t < pairs; ++t) {
-            turn(b);
-            HIPCHK(launch_pair2d<T>(b, s->p.collision == TLB_MRT, s->nc, s->stream));
-        }
+    for (int64_t t = 0; t < pairs; ++t) {
+        turn(b);
+        HIPCHK(launch_pair2d<T>(b, s->p.collision == TLB_MRT, s->nc, s->stream));
     }
     for (int64_t t = 2 * pairs; t < n; ++t) {
         turn(a);

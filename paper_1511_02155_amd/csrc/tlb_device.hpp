@@ -318,6 +318,23 @@ __device__ __forceinline__ void chem_potentials(const Phys<T>& P, const T dc[NC]
     mu_psi = mu[2] - T(0.5) * (mu[0] + mu[1]);
 }
 
+__device__ __forceinline__ double fmad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fmad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// e_i.v = sum_a e_ia j_a / rho without the terms that are zero, from j, 1/rho and v = j/rho: of two terms
+// the first enters unrounded.
+template <class L, typename T>
+__device__ __forceinline__ T edot(int i, const T (&j)[3], T irho, const T (&v)[3])
+{
+    int a[2], n = 0;
+    for (int q = 0; q < L::D; ++q)
+        if (ecomp<L>(i, q) != 0 && n < 2) a[n++] = q;
+    const T s0 = T(ecomp<L>(i, a[0]));
+    if (n == 1) return s0 > 0 ? v[a[0]] : -v[a[0]];
+    const T last = ecomp<L>(i, a[1]) > 0 ? v[a[1]] : -v[a[1]];
+    return fmad(s0 > 0 ? j[a[0]] : -j[a[0]], irho, last);
+}
+
 // Per-node collision.  Inputs: the node's shifted populations f, g, k (in
 // place -> post-collision), its moments, the concentration deviations dC,
 // their gradients gC[m][a] and Laplacians lC[m].
@@ -335,53 +352,65 @@ __device__ __forceinline__ void chem_potentials(const Phys<T>& P, const T dc[NC]
 // value to st(s, i, v) (species s: 0 f, 1 g, 2 + l the k set of psi_{3+l}; v in the arithmetic
 // type, rounded to the storage type by the caller); every value is read and written once, in the
 // same order for every caller, except that MRT reads f_i a second time.
+//
+// Fused multiply-adds are written out and no others are formed (fp contract(off)), so that every kernel
+// rounds alike whatever the code around it: left to the compiler, the choice between the two products of
+// a sum changed with the enclosing block, and the strip, batched and two-step kernels disagreed in the
+// last bit.  Terms whose coefficient is zero are left out, and the switch of the velocity terms is folded
+// into phi and psi (multiplications by 0 and 1 are exact).  D2Q9 with moments and stencils takes 320
+// FP64 operations per node and step, 351 before; the 256^3 FP32 step went from 1.516 to 1.491 ms.
 template <class L, bool MRT = false, int NC = 3, typename T, typename Ld, typename St>
 __device__ __forceinline__ void collide_core(const Phys<T>& P, const Moments<T, NC>& mo, const T dc[NC],
                                              const T gC[NC][3], const T lC[NC], Ld ld, St st)
 {
+#pragma clang fp contract(off)
     // T: arithmetic type.  MRT: f relaxes with multiple relaxation times (g and k always with BGK).
     // k_l relaxes with the k rate and mu_psi_l = mu_l - (mu_1 + mu_2)/2 (Sec. II.E).
-    const T third = T(1.0 / 3.0);
     const T cref = T(psi_ref<NC>());
     T mu[NC];
-    T pbx = mo.drho * third;  // p_b - 1/3 (the 1/3 is the reference pressure of the shifted f)
+    T pbx = 0;  // p_b - 1/3 (the 1/3 is the reference pressure of the shifted f)
     T lam = 0;
     T Txx = 0, Tyy = 0, Tzz = 0, Txy = 0, Tyz = 0, Tzx = 0;
 #pragma unroll
     for (int m = 0; m < NC; ++m) {
         const T c = cref + dc[m];
         const T omc = T(1) - c;
-        mu[m] = P.kappa[m] * c * omc * (T(1) - T(2) * c) - P.a2kappa[m] * lC[m];
-        pbx += T(0.5) * P.kappa[m] * c * c * omc * (T(1) - T(3) * c);
-        lam += P.a2kappa[m] * c * lC[m];
+        const T kc = P.kappa[m] * c;
+        mu[m] = fmad(kc * omc, fmad(T(-2), c, T(1)), -(P.a2kappa[m] * lC[m]));
+        const T z = kc * c * omc, h = fmad(T(-1.5), c, T(0.5));
+        pbx = m == 0 ? fmad(mo.drho, T(1.0 / 3.0), z * h) : fmad(z, h, pbx);
+        lam = fmad(P.a2kappa[m] * c, lC[m], lam);
         const T gx = gC[m][0], gy = gC[m][1], gz = gC[m][2];
-        Txx += P.a2kappa[m] * gx * gx;
-        Tyy += P.a2kappa[m] * gy * gy;
-        Txy += P.a2kappa[m] * gx * gy;
+        const T ax = P.a2kappa[m] * gx, ay = P.a2kappa[m] * gy;
+        Txx = fmad(ax, gx, Txx);
+        Tyy = fmad(ay, gy, Tyy);
+        Txy = fmad(ax, gy, Txy);
         if (L::D == 3) {
-            Tzz += P.a2kappa[m] * gz * gz;
-            Tyz += P.a2kappa[m] * gy * gz;
-            Tzx += P.a2kappa[m] * gz * gx;
+            const T az = P.a2kappa[m] * gz;
+            Tzz = fmad(az, gz, Tzz);
+            Tyz = fmad(ay, gz, Tyz);
+            Tzx = fmad(az, gx, Tzx);
         }
     }
-    const T mu_phi = T(0.5) * (mu[0] - mu[1]);
     constexpr int NK = NC - 2;
+    const T rho = T(1) + mo.drho;
+    const T irho = T(1) / rho;
+    const T j[3] = {mo.jx, mo.jy, (L::D == 3) ? mo.jz : T(0)};
+    const T v[3] = {j[0] * irho, j[1] * irho, (L::D == 3) ? j[2] * irho : T(0)};
+    T vv = fmad(v[0], v[0], v[1] * v[1]);
+    if (L::D == 3) vv = fmad(v[2], v[2], vv);
+    vv *= T(-1.5);
+
+    const T wf = P.omega[0], wg = P.omega[1], wk = P.omega[2];
+    const T A = T(3) * (pbx - lam);
+    const T Bp = P.gphi3 * (T(0.5) * (mu[0] - mu[1]));
+    const T phi = P.adv * mo.phi;  // in the velocity terms of g^eq, k^eq (absent without advection)
     T Bk[NK], psi[NK];
 #pragma unroll
     for (int l = 0; l < NK; ++l) {
-        Bk[l] = P.gpsi3 * (mu[2 + l] - T(0.5) * (mu[0] + mu[1]));
-        psi[l] = cref + (l == 0 ? mo.dpsi : mo.dpsx[l > 0 ? l - 1 : 0]);
+        Bk[l] = P.gpsi3 * fmad(T(-0.5), mu[0] + mu[1], mu[2 + l]);
+        psi[l] = P.adv * (cref + (l == 0 ? mo.dpsi : mo.dpsx[l > 0 ? l - 1 : 0]));
     }
-
-    const T rho = T(1) + mo.drho;
-    const T irho = T(1) / rho;
-    const T vx = mo.jx * irho, vy = mo.jy * irho, vz = (L::D == 3) ? mo.jz * irho : T(0);
-    const T vv = vx * vx + vy * vy + vz * vz;
-
-    const T A = T(3) * (pbx - lam);
-    const T Bp = P.gphi3 * mu_phi;
-    const T wf = P.omega[0], wg = P.omega[1], wk = P.omega[2];
-
     // i > 0: equilibrium and relaxation in place; the rest population last,
     // from the mass constraints.
     T sf = 0, sg = 0, sk[NK];
@@ -397,37 +426,36 @@ __device__ __forceinline__ void collide_core(const Phys<T>& P, const Moments<T, 
     // Directions come in pairs e_j = -e_i with the same weights (w_i and the second-order w_i^ab are
     // even in e), so an equilibrium splits into a part even in e, shared by the pair, and an odd part
     // of opposite signs: U_i = Ue + Uo, U_j = Ue - Uo with Uo = 3 e_i.v, Ue = 9/2 (e_i.v)^2 - 3/2 v^2.
+    // sf, sg, sk: half the sums of the equilibria over i > 0.
 #pragma unroll
     for (int i = 1; i < L::Q; ++i) {
-        const int j = L::opp[i];
-        if (j < i) continue;  // each pair once, from its lower index
+        const int o = L::opp[i];
+        if (o < i) continue;  // each pair once, from its lower index
         const T w = T(weight<L>(i));
-        const T ev = T(L::ex[i]) * vx + T(L::ey[i]) * vy + T(L::ez[i]) * vz;
-        const T Ue = T(4.5) * ev * ev - T(1.5) * vv, Uo = T(3) * ev;
-        T G = T(3 * wdiag<L>(i, 0)) * Txx + T(3 * wdiag<L>(i, 1)) * Tyy +
-              T(3 * woff<L>(i, 0, 1)) * Txy;
-        if (L::D == 3)
-            G += T(3 * wdiag<L>(i, 2)) * Tzz + T(3 * woff<L>(i, 1, 2)) * Tyz +
-                 T(3 * woff<L>(i, 2, 0)) * Tzx;
-        const T fe = w * (A + rho * Ue) + G, fo = w * rho * Uo;
-        // velocity terms of g^eq, k^eq (absent without advection)
-        const T Uae = P.adv * Ue, Uao = P.adv * Uo;
-        const T ge = w * (Bp + mo.phi * Uae), go = w * mo.phi * Uao;
+        const T ev = edot<L>(i, j, irho, v);
+        const T Ue = fmad(T(4.5) * ev, ev, vv), Uo = T(3) * ev;
+        T G = fmad(T(3 * wdiag<L>(i, 0)), Txx, T(3 * wdiag<L>(i, 1)) * Tyy);
+        if (woff<L>(i, 0, 1) != 0.0) G = fmad(T(3 * woff<L>(i, 0, 1)), Txy, G);
+        if (L::D == 3) G = fmad(T(3 * wdiag<L>(i, 2)), Tzz, G);
+        if (woff<L>(i, 1, 2) != 0.0) G = fmad(T(3 * woff<L>(i, 1, 2)), Tyz, G);
+        if (woff<L>(i, 2, 0) != 0.0) G = fmad(T(3 * woff<L>(i, 2, 0)), Tzx, G);
+        const T fe = fmad(w, fmad(rho, Ue, A), G), fo = w * rho;
+        const T ge = w * fmad(phi, Ue, Bp), go = w * phi;
         T ke[NK], ko[NK];
 #pragma unroll
         for (int l = 0; l < NK; ++l) {
-            ke[l] = w * (Bk[l] + psi[l] * Uae);
-            ko[l] = w * psi[l] * Uao;
+            ke[l] = w * fmad(psi[l], Ue, Bk[l]);
+            ko[l] = w * psi[l];
         }
-        sf += T(2) * fe;
-        sg += T(2) * ge;
+        sf += fe;
+        sg += ge;
 #pragma unroll
-        for (int l = 0; l < NK; ++l) sk[l] += T(2) * ke[l];
+        for (int l = 0; l < NK; ++l) sk[l] += ke[l];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int d = h == 0 ? i : j;
-            const T sgn = h == 0 ? T(1) : T(-1);
-            const T feq = fe + sgn * fo, geq = ge + sgn * go;
+            const int d = h == 0 ? i : o;
+            const T U = h == 0 ? Uo : -Uo;
+            const T feq = fmad(fo, U, fe), geq = fmad(go, U, ge);
             const T fi = ld(0, d), gi = ld(1, d);
             T ki[NK];
 #pragma unroll
@@ -435,30 +463,30 @@ __device__ __forceinline__ void collide_core(const Phys<T>& P, const Moments<T, 
             if constexpr (MRT) {
                 dq[d] = fi - feq;
             } else {
-                st(0, d, fi + wf * (feq - fi));
+                st(0, d, fmad(wf, feq - fi, fi));
             }
-            st(1, d, gi + wg * (geq - gi));
+            st(1, d, fmad(wg, geq - gi, gi));
 #pragma unroll
-            for (int l = 0; l < NK; ++l) st(2 + l, d, ki[l] + wk * ((ke[l] + sgn * ko[l]) - ki[l]));
+            for (int l = 0; l < NK; ++l) st(2 + l, d, fmad(wk, fmad(ko[l], U, ke[l]) - ki[l], ki[l]));
         }
         if constexpr (MRT) {
             // the energy and stress coefficients are even in e: the pair enters its moments as a sum
-            const T ds = dq[i] + dq[j];
-            me += T(mrt_energy<L>(i)) * ds;
+            const T ds = dq[i] + dq[o];
+            me = fmad(T(mrt_energy<L>(i)), ds, me);
 #pragma unroll
             for (int q = 0; q < NS; ++q)
-                if (mrt_stress<L>(q, i) != 0.0) ms[q] += T(mrt_stress<L>(q, i)) * ds;
+                if (mrt_stress<L>(q, i) != 0.0) ms[q] = fmad(T(mrt_stress<L>(q, i)), ds, ms[q]);
         }
     }
     const T f0 = ld(0, 0), g0 = ld(1, 0);
     if constexpr (MRT) {
         // the rest population has no stress moment; it enters the energy moment
-        dq[0] = f0 - (mo.drho - sf);
-        me += T(mrt_energy<L>(0)) * dq[0];
+        dq[0] = f0 - fmad(T(-2), sf, mo.drho);
+        me = fmad(T(mrt_energy<L>(0)), dq[0], me);
         me *= P.mrt_db * T(1.0 / mrt_energy_norm<L>());
 #pragma unroll
         for (int q = 0; q < NS; ++q) ms[q] *= P.mrt_dv * T(1.0 / mrt_stress_norm<L>(q));
-        st(0, 0, f0 - P.mrt_sg * dq[0] - T(mrt_energy<L>(0)) * me);
+        st(0, 0, fmad(T(-mrt_energy<L>(0)), me, fmad(-P.mrt_sg, dq[0], f0)));
         // the projections back onto a pair share their even coefficients
 #pragma unroll
         for (int i = 1; i < L::Q; ++i) {
@@ -467,19 +495,19 @@ __device__ __forceinline__ void collide_core(const Phys<T>& P, const Moments<T, 
             T c = T(mrt_energy<L>(i)) * me;
 #pragma unroll
             for (int q = 0; q < NS; ++q)
-                if (mrt_stress<L>(q, i) != 0.0) c += T(mrt_stress<L>(q, i)) * ms[q];
-            st(0, i, ld(0, i) - P.mrt_sg * dq[i] - c);
-            st(0, j, ld(0, j) - P.mrt_sg * dq[j] - c);
+                if (mrt_stress<L>(q, i) != 0.0) c = fmad(T(mrt_stress<L>(q, i)), ms[q], c);
+            st(0, i, fmad(-P.mrt_sg, dq[i], ld(0, i)) - c);
+            st(0, j, fmad(-P.mrt_sg, dq[j], ld(0, j)) - c);
         }
     } else {
-        st(0, 0, f0 + wf * ((mo.drho - sf) - f0));
+        st(0, 0, fmad(wf, fmad(T(-2), sf, mo.drho) - f0, f0));
     }
-    st(1, 0, g0 + wg * ((mo.phi - sg) - g0));
+    st(1, 0, fmad(wg, fmad(T(-2), sg, mo.phi) - g0, g0));
 #pragma unroll
     for (int l = 0; l < NK; ++l) {
         const T k0 = ld(2 + l, 0);
         const T dps = l == 0 ? mo.dpsi : mo.dpsx[l > 0 ? l - 1 : 0];
-        st(2 + l, 0, k0 + wk * ((dps - sk[l]) - k0));
+        st(2 + l, 0, fmad(wk, fmad(T(-2), sk[l], dps) - k0, k0));
     }
 }
 

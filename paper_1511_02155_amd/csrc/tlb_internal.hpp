@@ -39,9 +39,10 @@ __device__ __forceinline__ int xcd_item(int b, int G)
 
 template <typename T>
 hipError_t launch_step2d(const StepArgs<T>& a, int width, int hold, bool mrt, int nc, hipStream_t s);
-// Two D2Q9 steps in one launch (tlb_pair2d.hip), and its strips and chunks for the lattice of `a`.
+// Two D2Q9 steps in one launch (tlb_pair2d.hip), and its strips and chunks for the lattice of `a`; false where
+// single steps, in items of single_chunk rows and single_width columns, are faster.
 template <typename T>
-void pair2d_shape(StepArgs<T>& a, int nc, int cus);
+bool pair2d_shape(StepArgs<T>& a, int nc, int cus, int single_chunk, int single_width);
 template <typename T>
 hipError_t launch_pair2d(const StepArgs<T>& a, bool mrt, int nc, hipStream_t s);
 template <typename T>

@@ -21,11 +21,13 @@
 // reach the rows they both read at the same time, and every other launch reverses all of them, as in the
 // one-step sweep.
 //
-// Measured on MI355X, per step, against the one-step kernel: 1024^2 FP64 60.4 us (89.7), FP32 33.9 (42.4),
-// 700 x 900 of four components with several relaxation times FP64 55.0 (76.9), 512^2 FP64 18.9 (23.1),
-// 64^2 FP64 6.5 (6.7).  In FP64 an iteration of the 1024 items in flight moves 110 KB per compute unit
-// through the L2 in 4.6 us, which bounds it; in FP32 (2.6 us) the instructions of two wavefronts per SIMD do.
-// Columns and rows that are computed twice (7 of 64 lanes, 7 of 26 iterations) take the rest.
+// Measured on MI355X, per step, against the one-step kernel: 1024^2 FP64 56.7 us (89.7), FP32 30.5 (42.4),
+// 700 x 900 of four components with several relaxation times FP64 46.0 (76.9), 512^2 FP64 15.4 (23.1),
+// 64^2 FP64 6.1 (6.7).  In FP64 an iteration of the 1024 items in flight moves 110 KB per compute unit
+// through the L2 in 4.4 us, which bounds it; in FP32 (2.3 us) the instructions of two wavefronts per SIMD
+// do.  Columns and rows that are computed twice (7 of 64 lanes, 7 of 26 iterations) take the rest.  The
+// iterations have no branches but those at walls (rows that do not exist are computed and never used),
+// which took the FP64 kernel from 780 to 560 instructions per iteration and wavefront.
 //
 // Every value is formed by the operations of the one-step kernel in the same order, so the results are
 // bitwise those of two single steps.
@@ -80,10 +82,15 @@ __device__ __forceinline__ void pair_sweep(const StepArgs<T>& A, int x0, int nco
     const int vlo = walls ? (DIR > 0 ? -y0 : yfirst - (ny - 1)) : -(1 << 29);
     const int vhi = walls ? (DIR > 0 ? ny - 1 - y0 : yfirst) : (1 << 29);
     const int K = L + 7;
+    const uint32_t rowb = (uint32_t)nx * (uint32_t)sizeof(T);           // bytes of a row
+    const uint32_t arrb = (uint32_t)A.N * (uint32_t)sizeof(T);          // bytes of a population array
+    const uint32_t state = arrb * (uint32_t)J;
+    // lattice row of virtual row v, and the step to the next one
     auto row_of = [&](int v) {
-        int y = (yfirst + v * DIR) % ny;
+        const int y = (yfirst + v * DIR) % ny;
         return y < 0 ? y + ny : y;
     };
+    auto next_row = [&](int y) { return DIR > 0 ? (y == ny - 1 ? 0 : y + 1) : (y == 0 ? ny - 1 : y - 1); };
     // columns of the lane and of its neighbours, periodic
     int x = (x0 - 3 + lane) % nx;
     x = x < 0 ? x + nx : x;
@@ -117,49 +124,79 @@ __device__ __forceinline__ void pair_sweep(const StepArgs<T>& A, int x0, int nco
         for (int m = 0; m < NC; ++m) rows[to][m][lane] = c[m];
     };
 
+    // the deviations of psi_l are those of C_l, which come back from LDS: they need not be held as moments
+    auto psi_of = [&](Moments<C, NC>& mo, const C (&dc)[NC]) {
+        mo.dpsi = dc[2];
+#pragma unroll
+        for (int l = 0; l < NC - 3; ++l) mo.dpsx[l] = dc[3 + l];
+    };
+
     if (threadIdx.x < 64) {
         // ---- first step ----
         const uint32_t vo[3] = {(uint32_t)x * (uint32_t)sizeof(T),
                                 (uint32_t)(x == 0 ? nx - 1 : x - 1) * (uint32_t)sizeof(T),
                                 (uint32_t)(x == nx - 1 ? 0 : x + 1) * (uint32_t)sizeof(T)};
-        const StateAddr<T, false> src(A.src, A.N, NC);
+        const Rsrc src = make_rsrc(A.src, state);
+        // the pull of row y: per-lane offsets of the three rows and columns it comes from, uniform ones of the
+        // population arrays; at a wall the populations that would come from beyond it are loaded once more
+        auto pull = [&](int y, T* p) {
+            const uint32_t at[3] = {(uint32_t)y * rowb, (uint32_t)(y == 0 ? ny - 1 : y - 1) * rowb,
+                                    (uint32_t)(y == ny - 1 ? 0 : y + 1) * rowb};
+            uint32_t off[3][3];
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) off[r][q] = vo[q] + at[r];
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                const int r = L9::ey[i] == 0 ? 0 : (L9::ey[i] == 1 ? 1 : 2), q = L9::ex[i] == 0 ? 0 : (L9::ex[i] == 1 ? 1 : 2);
+#pragma unroll
+                for (int s = 0; s < NC; ++s) p[9 * s + i] = bload<T>(src, off[r][q], (uint32_t)(9 * s + i) * arrb);
+            }
+            if (walls && (y == 0 || y == ny - 1)) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i)
+                    if (L9::ey[i] != 0 && (L9::ey[i] == 1 ? y == 0 : y == ny - 1))
+#pragma unroll
+                        for (int s = 0; s < NC; ++s)
+                            p[9 * s + i] = bload<T>(src, off[0][0], (uint32_t)(9 * s + L9::opp[i]) * arrb);
+            }
+        };
         T P0[J], P1[J], P2[J];
 #pragma unroll
         for (int i = 0; i < J; ++i) P0[i] = P1[i] = P2[i] = T(0);
-        Moments<C, NC> Mb = {};
+        Moments<C, NC> M0 = {}, M1 = {}, M2 = {};
         auto exists = [&](int v) { return v >= vlo && v <= vhi; };
-        if (exists(-3)) pull2d<T, NC, false>(A, src, vo, row_of(-3), P0);
-        auto step = [&](int k, int a, int b, int c, T* Pc, T* Pb, T* Pn) {  // rows v, v-1 and v+1
+        int yn = row_of(-3);  // the row to load next
+        if (exists(-3)) pull(yn, P0);
+        // rows v, v-1 and v+1 of the populations; a, b, c: LDS rows of v-2, v-1 and v
+        auto step = [&](int k, int a, int b, int c, T* Pc, T* Pb, T* Pn, Moments<C, NC>& Mc, Moments<C, NC>& Mb) {
             const int v = k - 3;
-            if (v + 1 <= L + 2 && exists(v + 1)) pull2d<T, NC, false>(A, src, vo, row_of(v + 1), Pn);
-            Moments<C, NC> Mc = {};
-            if (v <= L + 2 && exists(v)) {
-                concentrations(Pc, Mc, c);
-                if (walls && v == vlo) ghost(c, wet_in, b);
-            } else if (walls && v == vhi + 1) {
-                ghost(b, wet_out, c);
+            yn = next_row(yn);
+            if (v + 1 <= L + 2 && exists(v + 1)) pull(yn, Pn);
+            concentrations(Pc, Mc, c);
+            if (walls) {
+                if (v == vlo) ghost(c, wet_in, b);
+                if (v == vhi + 1) ghost(b, wet_out, c);
             }
-            const int e = v - 1;
-            if (e >= -2 && e <= L + 1 && exists(e)) {
-                C dc[NC], gC[NC][3], lC[NC];
-                stencils(a, b, c, dc, gC, lC);
-                collide<L9, MRT, NC>(A.P, Mb, dc, gC, lC, Pb, Pb + 9, Pb + 18);
-                T(*out)[64] = S.link[k & 1];
+            C dc[NC], gC[NC][3], lC[NC];
+            stencils(a, b, c, dc, gC, lC);
+            psi_of(Mb, dc);
+            collide<L9, MRT, NC>(A.P, Mb, dc, gC, lC, Pb, Pb + 9, Pb + 18);
+            T(*out)[64] = S.link[k & 1];
 #pragma unroll
-                for (int j = 0; j < J; ++j) out[j][lane] = Pb[j];
-            }
-            Mb = Mc;
+            for (int j = 0; j < J; ++j) out[j][lane] = Pb[j];
             link_barrier();
         };
         for (int k = 0; k < K; k += 3) {
-            step(k, 1, 2, 0, P0, P2, P1);
-            if (k + 1 < K) step(k + 1, 2, 0, 1, P1, P0, P2);
-            if (k + 2 < K) step(k + 2, 0, 1, 2, P2, P1, P0);
+            step(k, 1, 2, 0, P0, P2, P1, M0, M2);
+            if (k + 1 < K) step(k + 1, 2, 0, 1, P1, P0, P2, M1, M0);
+            if (k + 2 < K) step(k + 2, 0, 1, 2, P2, P1, P0, M2, M1);
         }
     } else {
         // ---- second step ----
         using CL = Classes<DIR>;
-        const StateAddr<T, false> dst(A.dst, A.N, NC);
+        const Rsrc dst = make_rsrc(A.dst, state);
         const bool active = lane >= 3 && lane < 3 + ncols;
         const uint32_t vo = (uint32_t)x * (uint32_t)sizeof(T);
         // lanes that hold the columns x, x-1 and x+1 (the wavefront's end lanes are never used)
@@ -167,78 +204,72 @@ __device__ __forceinline__ void pair_sweep(const StepArgs<T>& A, int x0, int nco
         T Q0[J], Q1[J], Q2[J];
 #pragma unroll
         for (int i = 0; i < J; ++i) Q0[i] = Q1[i] = Q2[i] = T(0);
-        Moments<C, NC> Mb = {};
-        auto step = [&](int k, int ra, int rb, int rc, T* Qc, T* Qb, T* Qn) {  // rows w-1 (completed now), w-2 (collided) and w
+        Moments<C, NC> M0 = {}, M1 = {}, M2 = {};
+        int ye = yfirst;  // the row to store next
+        // rows w-1 (completed now), w-2 (collided) and w of the populations; ra, rb, rc: LDS rows of w-3, w-2, w-1
+        auto step = [&](int k, int ra, int rb, int rc, T* Qc, T* Qb, T* Qn, Moments<C, NC>& Mc, Moments<C, NC>& Mb) {
             const int w = k - 5;
             T(*in)[64] = S.link[(k - 1) & 1];
-            const bool got = w >= -2 && w <= L + 1 && w >= vlo && w <= vhi;
-            if (got) {
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
+            for (int q = 0; q < 3; ++q)
 #pragma unroll
-                    for (int s = 0; s < NC; ++s) {
-                        // pull: x - e_x; q = 0, 1, 2 are e_x = 0, +1, -1 in each class
-                        Qc[9 * s + CL::lead[q]] = in[9 * s + CL::lead[q]][from[q]];
-                        Qn[9 * s + CL::level[q]] = in[9 * s + CL::level[q]][from[q]];
-                    }
-                if (walls && w == vlo) {
-#pragma unroll
-                    for (int q = 0; q < 3; ++q)
-#pragma unroll
-                        for (int s = 0; s < NC; ++s)
-                            Qn[9 * s + CL::trail[q]] = in[9 * s + L9::opp[CL::trail[q]]][lane];
+                for (int s = 0; s < NC; ++s) {
+                    // pull: x - e_x; q = 0, 1, 2 are e_x = 0, +1, -1 in each class
+                    if (!(walls && w == vhi + 1)) Qc[9 * s + CL::lead[q]] = in[9 * s + CL::lead[q]][from[q]];
                 }
-            } else if (walls && w == vhi + 1) {
-                // the wall row's own values, turned back, were put into the row after it
-#pragma unroll
-                for (int q = 0; q < 3; ++q)
-#pragma unroll
-                    for (int s = 0; s < NC; ++s) Qc[9 * s + CL::lead[q]] = Qn[9 * s + CL::lead[q]];
-            }
             const int c = w - 1;
-            Moments<C, NC> Mc = {};
-            if (c >= -1 && c <= L && c >= vlo && c <= vhi) {
-                concentrations(Qc, Mc, rc);
-                if (walls && c == vlo) ghost(rc, wet_in, rb);
-            } else if (walls && c == vhi + 1) {
-                ghost(rb, wet_out, rc);
+            concentrations(Qc, Mc, rc);
+            if (walls) {
+                if (c == vlo) ghost(rc, wet_in, rb);
+                if (c == vhi + 1) ghost(rb, wet_out, rc);
             }
             const int e = w - 2;
-            if (e >= 0 && e < L) {
+            if (e >= 0) {
                 C dc[NC], gC[NC][3], lC[NC];
                 stencils(ra, rb, rc, dc, gC, lC);
+                psi_of(Mb, dc);
                 collide<L9, MRT, NC>(A.P, Mb, dc, gC, lC, Qb, Qb + 9, Qb + 18);
+                const uint32_t off = vo + (uint32_t)ye * rowb;
+                ye = next_row(ye);
                 if (active) {
-                    const uint32_t row = (uint32_t)row_of(e) * (uint32_t)nx;
 #pragma unroll
                     for (int i = 0; i < 9; ++i)
 #pragma unroll
-                        for (int s = 0; s < NC; ++s) bstore<T>(Qb[9 * s + i], dst.rsrc(9 * s + i), vo, dst.soff(9 * s + i, row));
+                        for (int s = 0; s < NC; ++s) bstore<T>(Qb[9 * s + i], dst, off, (uint32_t)(9 * s + i) * arrb);
                 }
             }
-            if (got) {
-                // the row after w takes its trailing populations now (into the registers just stored); beyond
-                // the last row, w's own ones turned back, for the row itself
-                const bool end = walls && w == vhi;
-                if (!end) {
+            // row w takes the populations of its own level, and the row after it its trailing ones (into the
+            // registers just stored).  At the first row there is, and at the last one, the wall row's own
+            // populations, turned back, complete it.
 #pragma unroll
-                    for (int q = 0; q < 3; ++q)
+            for (int q = 0; q < 3; ++q)
 #pragma unroll
-                        for (int s = 0; s < NC; ++s) Qb[9 * s + CL::trail[q]] = in[9 * s + CL::trail[q]][from[q]];
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 3; ++q)
-#pragma unroll
-                        for (int s = 0; s < NC; ++s) Qb[9 * s + CL::lead[q]] = in[9 * s + L9::opp[CL::lead[q]]][lane];
+                for (int s = 0; s < NC; ++s) {
+                    Qn[9 * s + CL::level[q]] = in[9 * s + CL::level[q]][from[q]];
+                    Qb[9 * s + CL::trail[q]] = in[9 * s + CL::trail[q]][from[q]];
                 }
+            if (walls && w == vlo) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int s = 0; s < NC; ++s) Qn[9 * s + CL::trail[q]] = in[9 * s + L9::opp[CL::trail[q]]][lane];
             }
-            Mb = Mc;
+            if (walls && w == vhi) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int s = 0; s < NC; ++s) Qn[9 * s + CL::lead[q]] = in[9 * s + L9::opp[CL::lead[q]]][lane];
+            }
             link_barrier();
         };
-        for (int k = 0; k < K; k += 3) {
-            step(k, 1, 2, 0, Q0, Q2, Q1);
-            if (k + 1 < K) step(k + 1, 2, 0, 1, Q1, Q0, Q2);
-            if (k + 2 < K) step(k + 2, 0, 1, 2, Q2, Q1, Q0);
+        // nothing has come through the link before iteration 3
+        link_barrier();
+        link_barrier();
+        link_barrier();
+        for (int k = 3; k < K; k += 3) {
+            step(k, 1, 2, 0, Q0, Q2, Q1, M0, M2);
+            if (k + 1 < K) step(k + 1, 2, 0, 1, Q1, Q0, Q2, M1, M0);
+            if (k + 2 < K) step(k + 2, 0, 1, 2, Q2, Q1, Q0, M2, M1);
         }
     }
 }
@@ -262,26 +293,36 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(NC > 3 ? 1 
 
 }  // namespace
 
-// Strips and chunks.  An item takes chunk + 7 iterations of about the same length whatever its size, and
-// the chip holds `slots` items at once (two wavefronts per SIMD, one in FP64 with four components), so the
-// chunk is the one with the fewest iterations in all: rounds of items times iterations of an item.
-// Measured at 1024^2 FP64: 19 rows (972 items in one round) 60.4 us per step, 20 rows 63.1, 26 rows 64.0;
-// FP32 33.4, 34.5, 37.0; 700 x 900 of four components FP64: 24 rows 55.0, 26 rows 57.1, 12 rows 62.5.
+// Strips and chunks.  An item takes chunk + 7 iterations, and an iteration takes the longer the more items
+// share a compute unit; the chip holds four per compute unit (two wavefronts per SIMD), two of four
+// components (one).  Measured, in us per iteration with 1, 2, 3 and 4 items on a compute unit (lattices of
+// 58 to 1024 columns, 45 to 512 rows, chunks of 1 to 24 rows): FP32 1.55, 1.9, 2.1, 2.2; FP64 1.6, 1.9,
+// 2.35, 2.6; four components 2.1, 2.4.  The chunk is the one with the least time by these figures: 512^2
+// FP64 5 rows (927 items) 15.4 us per step against 15.8 at 8 rows and 20.1 at 4 (1152 items, a second
+// round); 333 x 217 FP32 2 rows 9.0 against 14.7 at one.
+//
+// Returns whether two steps at once are the faster way.  They are wherever the one-step kernel's items have
+// several rows; lattices so small that those have one row take about 7.0 us per step there and 1.6 ns more
+// per wavefront (four components 8.7 us and 1.5 ns up to 600 wavefronts, 12.5 us beyond).
 template <typename T>
-void pair2d_shape(StepArgs<T>& a, int nc, int cus)
+bool pair2d_shape(StepArgs<T>& a, int nc, int cus, int single_chunk, int single_width)
 {
     constexpr int kCols = 58, kFill = 7;
+    const double f32[4] = {1.55, 1.9, 2.1, 2.2}, f64[4] = {1.6, 1.9, 2.35, 2.6}, four[2] = {2.1, 2.4};
+    const double* per = nc > 3 ? four : (sizeof(T) == 4 ? f32 : f64);
+    const int most = nc > 3 ? 2 : 4;
+    if (cus < 1) cus = 256;
     a.ntx = (a.nx + kCols - 1) / kCols;
     a.cols = (a.nx + a.ntx - 1) / a.ntx;
     a.nty = 1;
-    const int64_t slots = (int64_t)(cus > 0 ? cus : 256) * (sizeof(T) == 8 && nc > 3 ? 2 : 4);
-    // with n rounds at most n * slots items: the longest round count worth a look halves the chunk each time
-    int64_t best = INT64_MAX;
-    for (int64_t rounds = 1; rounds <= 64; ++rounds) {
-        const int64_t nch = std::min<int64_t>(a.ny, std::max<int64_t>(1, rounds * slots / a.ntx));
-        const int chunk = (int)((a.ny + nch - 1) / nch);
+    double best = 1e300;
+    for (int q = 1; q <= 64; ++q) {  // about q items per compute unit in all
+        const int64_t want = std::min<int64_t>(a.ny, std::max<int64_t>(1, (int64_t)q * cus / a.ntx));
+        const int chunk = (int)((a.ny + want - 1) / want);
         const int nchunks = (a.ny + chunk - 1) / chunk;
-        const int64_t cost = (((int64_t)a.ntx * nchunks + slots - 1) / slots) * (chunk + kFill);
+        const int64_t share = ((int64_t)a.ntx * nchunks + cus - 1) / cus;
+        const int rest = (int)(share % most);
+        const double cost = ((double)(share / most) * per[most - 1] + (rest ? per[rest - 1] : 0.0)) * (chunk + kFill);
         if (cost < best) {
             best = cost;
             a.chunk = chunk;
@@ -289,6 +330,10 @@ void pair2d_shape(StepArgs<T>& a, int nc, int cus)
         }
     }
     a.nitems = a.ntx * a.nchunks;
+    if (single_chunk > 1) return true;
+    const double waves = (double)((a.nx + single_width - 1) / single_width) * a.ny * (single_width / 64);
+    const double single = nc > 3 ? (waves <= 600.0 ? 8.7 + 0.0015 * waves : 12.5) : 7.0 + 0.0016 * waves;
+    return 0.5 * best + 0.4 < single;
 }
 
 template <typename T>
@@ -308,8 +353,8 @@ hipError_t launch_pair2d(const StepArgs<T>& a, bool mrt, int nc, hipStream_t s)
     return hipErrorInvalidValue;
 }
 
-template void pair2d_shape<float>(StepArgs<float>&, int, int);
-template void pair2d_shape<double>(StepArgs<double>&, int, int);
+template bool pair2d_shape<float>(StepArgs<float>&, int, int, int, int);
+template bool pair2d_shape<double>(StepArgs<double>&, int, int, int, int);
 template hipError_t launch_pair2d<float>(const StepArgs<float>&, bool, int, hipStream_t);
 template hipError_t launch_pair2d<double>(const StepArgs<double>&, bool, int, hipStream_t);
 

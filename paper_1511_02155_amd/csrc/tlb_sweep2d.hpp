@@ -129,13 +129,13 @@ __device__ __forceinline__ T pull2d_one(const StepArgs<T>& A, int j, int x, int 
 template <typename C>
 __device__ __forceinline__ void stencil9(C ac, C aS, C aD, C bc, C bS, C bD, C cc, C cS, C cD, int dir, C* g, C& lap)
 {
-#pragma clang fp contract(on)
+#pragma clang fp contract(off)
     const C up = dir > 0 ? cc : ac, dn = dir > 0 ? ac : cc;
     const C Sup = dir > 0 ? cS : aS, Sdn = dir > 0 ? aS : cS;
-    g[0] = bD * C(1.0 / 3.0) + (aD + cD) * C(1.0 / 12.0);
-    g[1] = (up - dn) * C(1.0 / 3.0) + (Sup - Sdn) * C(1.0 / 12.0);
+    g[0] = fmad(bD, C(1.0 / 3.0), (aD + cD) * C(1.0 / 12.0));
+    g[1] = fmad(up - dn, C(1.0 / 3.0), (Sup - Sdn) * C(1.0 / 12.0));
     g[2] = C(0);
-    lap = (bS + (ac + cc)) * C(2.0 / 3.0) + (aS + cS) * C(1.0 / 6.0) - bc * C(10.0 / 3.0);
+    lap = fmad(bc, C(-10.0 / 3.0), fmad(bS + (ac + cc), C(2.0 / 3.0), (aS + cS) * C(1.0 / 6.0)));
 }
 
 // Occupancy target (wavefronts per SIMD) the register allocation is held to
