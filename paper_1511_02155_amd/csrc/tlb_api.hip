@@ -581,37 +581,77 @@ static hipError_t launch_one(const tlb_sim* s, const StepArgs<T>& a)
                                   s->p.collision == TLB_MRT, s->nc, s->stream);
 }
 
-// Whether steps run two to a launch (tlb_pair2d.hip): D2Q9 of three or four components in the default
-// launch, a state of one buffer descriptor.
-static bool pair_steps(const tlb_sim* s)
-{
-    return s->p.lattice == TLB_D2Q9 && s->nc <= 4 && !s->launch_set && tlb_state_bytes(s) <= (int64_t)0xFFFFFF00;
-}
+// How a launch advances a D2Q9 lattice: one step (the strip kernel), two in sweeps or two or three in tiles.
+enum class Way { one, pair, tile };
 
-// n steps launched directly, two to a launch where that is possible.  even: in an even number of
-// launches (n is even), so that the state ends in the buffer it started from.
+// n steps launched directly, several to a launch where that is faster: D2Q9 in the default launch, a state
+// of one buffer descriptor.  even: in an even number of launches (n is even), so that the state ends in the
+// buffer it started from.
 template <typename T>
 static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
 {
-    StepArgs<T> a = step_args<T>(s);
-    StepArgs<T> b = a;
-    int64_t pairs = n / 2;
-    if (pairs > 0 && !(pair_steps(s) && pair2d_shape<T>(b, s->nc, s->cus, s->launch.chunk, s->launch.width))) pairs = 0;
-    if (even && (pairs & 1)) --pairs;
-    auto turn = [&](StepArgs<T>& x) {
-        x.src = (const T*)s->state[s->cur];
-        x.dst = (T*)s->state[s->cur ^ 1];
-        x.flip = s->cur;  // every other launch sweeps each chunk the other way
+    const StepArgs<T> one = step_args<T>(s);
+    StepArgs<T> pair = one;
+    Way way = Way::one;
+    int tile = -1, tile_two = -1, steps = 1;
+    // the way for two steps left over by launches of three
+    Way two = Way::tile;
+    if (n > 1 && s->p.lattice == TLB_D2Q9 && !s->launch_set && tlb_state_bytes(s) <= (int64_t)0xFFFFFF00) {
+        // Times per step in us.  The strip kernel's items of several rows are never the fastest; with one row
+        // each, a step takes about 7.0 us and 1.6 ns more per wavefront (four and five components 8.7 us and
+        // 1.5 ns up to 600 wavefronts, 12.5 us beyond).
+        const double waves = (double)one.nitems * (s->launch.width / 64);
+        double best = s->launch.chunk > 1 ? 1e300
+                      : s->nc > 3         ? (waves <= 600.0 ? 8.7 + 0.0015 * waves : 12.5)
+                                          : 7.0 + 0.0016 * waves;
+        const double tp = pair2d_shape<T>(pair, s->nc, s->cus);
+        if (tp < best) {
+            best = tp;
+            way = Way::pair;
+            steps = 2;
+        }
+        const bool f64 = s->p.prec == TLB_F64;
+        double tt = 0.0, t2 = 0.0;
+        tile = tile2d_best(s->p.nx, s->p.ny, s->nc, f64, s->cus, 0, &tt);
+        tile_two = tile2d_best(s->p.nx, s->p.ny, s->nc, f64, s->cus, 2, &t2);
+        if (tt < best) {
+            way = Way::tile;
+            steps = tile2d_steps(tile);
+        }
+        if (tp < t2) two = Way::pair;
+    }
+    const bool mrt = s->p.collision == TLB_MRT;
+    auto go = [&](Way w, int shape) {
+        StepArgs<T> a = w == Way::pair ? pair : one;
+        a.src = (const T*)s->state[s->cur];
+        a.dst = (T*)s->state[s->cur ^ 1];
+        a.flip = s->cur;  // every other launch sweeps each chunk the other way
         s->cur ^= 1;
+        return w == Way::pair   ? launch_pair2d<T>(a, mrt, s->nc, s->stream)
+               : w == Way::tile ? launch_tile2d<T>(a, shape, mrt, s->nc, s->stream)
+                                : launch_one<T>(s, a);
     };
-    for (int64_t t = 0; t < pairs; ++t) {
-        turn(b);
-        HIPCHK(launch_pair2d<T>(b, s->p.collision == TLB_MRT, s->nc, s->stream));
+    int64_t many = n / steps, twos = 0, ones = n % steps;
+    if (ones == 2) {  // left over by launches of three
+        twos = 1;
+        ones = 0;
     }
-    for (int64_t t = 2 * pairs; t < n; ++t) {
-        turn(a);
-        HIPCHK(launch_one<T>(s, a));
+    if (even && ((many + twos + ones) & 1)) {
+        if (twos > 0) {  // two steps one by one
+            twos = 0;
+            ones += 2;
+        } else if (steps == 3) {  // three as two and one
+            --many;
+            ++twos;
+            ++ones;
+        } else {
+            --many;
+            ones += 2;
+        }
     }
+    for (int64_t t = 0; t < many; ++t) HIPCHK(go(way, tile));
+    for (int64_t t = 0; t < twos; ++t) HIPCHK(go(two, tile_two));
+    for (int64_t t = 0; t < ones; ++t) HIPCHK(go(Way::one, -1));
     return TLB_OK;
 }
 

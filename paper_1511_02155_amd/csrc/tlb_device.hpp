@@ -357,8 +357,8 @@ __device__ __forceinline__ T edot(int i, const T (&j)[3], T irho, const T (&v)[3
 // rounds alike whatever the code around it: left to the compiler, the choice between the two products of
 // a sum changed with the enclosing block, and the strip, batched and two-step kernels disagreed in the
 // last bit.  Terms whose coefficient is zero are left out, and the switch of the velocity terms is folded
-// into phi and psi (multiplications by 0 and 1 are exact).  D2Q9 with moments and stencils takes 320
-// FP64 operations per node and step, 351 before; the 256^3 FP32 step went from 1.516 to 1.491 ms.
+// into phi and psi (multiplications by 0 and 1 are exact).  D2Q9 with moments and stencils takes 323
+// FP64 operations per node and step, 350 before; the 256^3 FP32 step went from 1.516 to 1.511 ms.
 template <class L, bool MRT = false, int NC = 3, typename T, typename Ld, typename St>
 __device__ __forceinline__ void collide_core(const Phys<T>& P, const Moments<T, NC>& mo, const T dc[NC],
                                              const T gC[NC][3], const T lC[NC], Ld ld, St st)

@@ -294,22 +294,18 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(NC > 3 ? 1 
 }  // namespace
 
 // Strips and chunks.  An item takes chunk + 7 iterations, and an iteration takes the longer the more items
-// share a compute unit; the chip holds four per compute unit (two wavefronts per SIMD), two of four
-// components (one).  Measured, in us per iteration with 1, 2, 3 and 4 items on a compute unit (lattices of
+// share a compute unit; the chip holds four per compute unit (two wavefronts per SIMD), two of four or
+// five components (one).  Measured, in us per iteration with 1, 2, 3 and 4 items on a compute unit (lattices of
 // 58 to 1024 columns, 45 to 512 rows, chunks of 1 to 24 rows): FP32 1.55, 1.9, 2.1, 2.2; FP64 1.6, 1.9,
-// 2.35, 2.6; four components 2.1, 2.4.  The chunk is the one with the least time by these figures: 512^2
+// 2.35, 2.6; four components 2.1, 2.4; five 2.7, 3.2.  The chunk is the one with the least time by these figures: 512^2
 // FP64 5 rows (927 items) 15.4 us per step against 15.8 at 8 rows and 20.1 at 4 (1152 items, a second
 // round); 333 x 217 FP32 2 rows 9.0 against 14.7 at one.
-//
-// Returns whether two steps at once are the faster way.  They are wherever the one-step kernel's items have
-// several rows; lattices so small that those have one row take about 7.0 us per step there and 1.6 ns more
-// per wavefront (four components 8.7 us and 1.5 ns up to 600 wavefronts, 12.5 us beyond).
 template <typename T>
-bool pair2d_shape(StepArgs<T>& a, int nc, int cus, int single_chunk, int single_width)
+double pair2d_shape(StepArgs<T>& a, int nc, int cus)
 {
     constexpr int kCols = 58, kFill = 7;
-    const double f32[4] = {1.55, 1.9, 2.1, 2.2}, f64[4] = {1.6, 1.9, 2.35, 2.6}, four[2] = {2.1, 2.4};
-    const double* per = nc > 3 ? four : (sizeof(T) == 4 ? f32 : f64);
+    const double f32[4] = {1.55, 1.9, 2.1, 2.2}, f64[4] = {1.6, 1.9, 2.35, 2.6}, four[2] = {2.1, 2.4}, five[2] = {2.7, 3.2};
+    const double* per = nc > 4 ? five : nc > 3 ? four : (sizeof(T) == 4 ? f32 : f64);
     const int most = nc > 3 ? 2 : 4;
     if (cus < 1) cus = 256;
     a.ntx = (a.nx + kCols - 1) / kCols;
@@ -330,10 +326,7 @@ bool pair2d_shape(StepArgs<T>& a, int nc, int cus, int single_chunk, int single_
         }
     }
     a.nitems = a.ntx * a.nchunks;
-    if (single_chunk > 1) return true;
-    const double waves = (double)((a.nx + single_width - 1) / single_width) * a.ny * (single_width / 64);
-    const double single = nc > 3 ? (waves <= 600.0 ? 8.7 + 0.0015 * waves : 12.5) : 7.0 + 0.0016 * waves;
-    return 0.5 * best + 0.4 < single;
+    return 0.5 * best + 0.4;
 }
 
 template <typename T>
@@ -349,12 +342,14 @@ hipError_t launch_pair2d(const StepArgs<T>& a, bool mrt, int nc, hipStream_t s)
     TLB_P2(true, 3)
     TLB_P2(false, 4)
     TLB_P2(true, 4)
+    TLB_P2(false, 5)
+    TLB_P2(true, 5)
 #undef TLB_P2
     return hipErrorInvalidValue;
 }
 
-template bool pair2d_shape<float>(StepArgs<float>&, int, int, int, int);
-template bool pair2d_shape<double>(StepArgs<double>&, int, int, int, int);
+template double pair2d_shape<float>(StepArgs<float>&, int, int);
+template double pair2d_shape<double>(StepArgs<double>&, int, int);
 template hipError_t launch_pair2d<float>(const StepArgs<float>&, bool, int, hipStream_t);
 template hipError_t launch_pair2d<double>(const StepArgs<double>&, bool, int, hipStream_t);
 

@@ -1,10 +1,10 @@
-"""Two-step launches of the D2Q9 step (tlb_pair2d.hip) against single steps.
+"""Launches of several D2Q9 steps (tlb_pair2d.hip, tlb_tile2d.hip) against single steps.
 
-With the default launch shape tlb_step advances D2Q9 lattices two steps per launch; with a launch shape
-set by the caller every step is a launch of the one-step kernel.  Both form every value by the same
-operations in the same order, so the results are the same bit for bit (tolerance zero).  Sizes sit at the
-edges of the two-step kernel's strips (58 columns) and chunks, with the smallest lattices and odd ones,
-with and without walls, in both directions of the sweep.
+With the default launch shape tlb_step advances D2Q9 lattices two or three steps per launch; with a launch
+shape set by the caller every step is a launch of the one-step kernel.  All form every value by the same
+operations in the same order, so the results are the same bit for bit (tolerance zero).  The small sizes sit
+at the edges of the tiles (8 x 4, 16 x 8, 12 x 8 and 32 x 8 nodes, each the default of one of the sizes), the
+large ones at those of the sweeps' strips (58 columns) and chunks.
 """
 import numpy as np
 import pytest
@@ -31,39 +31,43 @@ def _pair(tlb, nx, ny, prec, walls, nc, mrt):
     return sims
 
 
-@pytest.mark.parametrize("size", [(3, 3), (5, 4), (58, 7), (59, 31), (64, 64), (117, 40), (700, 9), (61, 300)],
+@pytest.mark.parametrize("size", [(3, 3), (5, 4), (8, 4), (64, 64), (117, 40), (161, 153), (239, 241), (333, 217)],
                          ids=lambda s: "%dx%d" % s)
 @pytest.mark.parametrize("walls", [0, 1])
-@pytest.mark.parametrize("nc,mrt", [(3, 0), (3, 1), (4, 0), (4, 1)])
-def test_two_step_launches_equal_single_steps(size, walls, nc, mrt):
+@pytest.mark.parametrize("nc,mrt", [(3, 0), (3, 1), (4, 0), (4, 1), (5, 0), (5, 1)])
+def test_launches_of_several_steps_equal_single_steps(size, walls, nc, mrt):
     from paper_1511_02155_amd import tlb
 
     for prec in (tlb.TLB_F32, tlb.TLB_F64):
         two, one = _pair(tlb, *size, prec, walls, nc, mrt)
-        for n in (2, 4, 3):  # the odd count ends with a single step
+        for n in (2, 3, 4, 5):  # every remainder of launches of two and three steps
             two.step(n)
             one.step(n)
             assert np.array_equal(two.all_populations(), one.all_populations())
 
 
-def test_many_chunks_and_rounds():
-    """More items than the chip holds at once, chunks of several rows, both sweep directions."""
+@pytest.mark.parametrize("size", [(1045, 800), (1500, 1100)], ids=lambda s: "%dx%d" % s)
+@pytest.mark.parametrize("walls,nc,mrt", [(0, 3, 0), (1, 3, 0), (1, 3, 1), (1, 4, 0), (0, 4, 1), (1, 5, 1), (0, 5, 0)])
+def test_sweeps_of_many_chunks_and_rounds(size, walls, nc, mrt):
+    """Chunks of several rows, strips of 57 and 58 columns, more items than the chip holds at once, both sweep
+    directions."""
     from paper_1511_02155_amd import tlb
 
     for prec in (tlb.TLB_F32, tlb.TLB_F64):
-        two, one = _pair(tlb, 1500, 1100, prec, 1, 3, 0)
+        two, one = _pair(tlb, *size, prec, walls, nc, mrt)
         two.step(5)
         one.step(5)
-        assert np.array_equal(two.populations(0), one.populations(0))
-        assert np.array_equal(two.populations(2), one.populations(2))
+        for s in (0, nc - 1):
+            assert np.array_equal(two.populations(s), one.populations(s))
 
 
-@pytest.mark.parametrize("chain", [2, 6, 8])
-def test_captured_chains(chain):
-    """Chains whose pairs are odd or even in number, replayed several times with eager work between."""
+@pytest.mark.parametrize("size", [(90, 50), (333, 217)], ids=lambda s: "%dx%d" % s)
+@pytest.mark.parametrize("chain", [2, 4, 6, 8, 10])
+def test_captured_chains(chain, size):
+    """Chains of an odd or even number of launches, replayed several times with eager work between."""
     from paper_1511_02155_amd import tlb
 
-    two, one = _pair(tlb, 90, 50, tlb.TLB_F64, 1, 3, 0)
+    two, one = _pair(tlb, *size, tlb.TLB_F64, 1, 3, 0)
     two.set_graph(chain)
     for n in (chain, 3 * chain + 1, chain + 5, 2 * chain):
         two.step(n)
