@@ -21,13 +21,15 @@
 #include <string.h>
 
 #include <algorithm>
+#include <functional>
 #include <new>
 #include <numeric>
+#include <queue>
 #include <string>
 #include <vector>
 
 #include "../../include/tlb.h"
-#include "tlb_sweep2d.hpp"
+#include "tlb_pair2d.hpp"
 
 namespace tlb {
 
@@ -37,6 +39,7 @@ struct DomDesc {
     int64_t wet_off;  // element offset of its wetting array, or -1 (no walls)
     int32_t nx, ny, walls, chunk, ntx, nchunks;
     int32_t flat;  // 0: strip sweep (chunk = rows per item); 1: flat sweep (chunk = segments per item)
+    int32_t pair_cols, pair_chunk;  // two-step launches: columns and rows of an item
     Phys<acc_t<T>> P;
 };
 
@@ -285,6 +288,36 @@ void k_batch2d(BatchArgs<T> B)
     }
 }
 
+// Two steps of the whole batch in one launch: each workgroup takes one item (a strip of a domain's columns
+// over a chunk of its rows) and runs the two-step sweep of the single lattice on it, so that two steps read
+// and write the state once.  Items are dealt to the XCDs (blocks b, b + 8, ... of queue b mod 8) whole
+// domains at a time, balanced by their rows; a queue shorter than the longest ends in empty items.
+// 512 domains of 32 to 256 nodes a side, FP32: 356 us per step against 565 in tuned one-step launches.
+template <typename T>
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k_batch_pair2d(BatchArgs<T> B)
+{
+    __shared__ PairLds<T, 3> S;
+    const int2 w = B.items[blockIdx.x];
+    if (w.x < 0) return;
+    const DomDesc<T>& D = B.doms[w.x];
+    StepArgs<T> A;
+    A.src = B.src + D.off;
+    A.dst = B.dst + D.off;
+    A.wet = D.wet_off >= 0 ? B.wet + D.wet_off : nullptr;
+    A.nx = D.nx;
+    A.ny = D.ny;
+    A.walls = D.walls;
+    A.N = (int64_t)D.nx * D.ny;
+    A.P = D.P;
+    const int strip = w.y >> 16, chunk = w.y & 0xffff;
+    const int x0 = strip * D.pair_cols, ncols = min(D.pair_cols, D.nx - x0);
+    const int y0 = chunk * D.pair_chunk, L = min(D.pair_chunk, D.ny - y0);
+    if (((chunk ^ B.parity) & 1) == 0)
+        pair_sweep<T, 1, false, 3>(A, x0, ncols, y0, L, S);
+    else
+        pair_sweep<T, -1, false, 3>(A, x0, ncols, y0, L, S);
+}
+
 template <typename T>
 static hipError_t launch_batch2d(const BatchArgs<T>& a, int width, int depth, int grid, hipStream_t s)
 {
@@ -347,6 +380,13 @@ struct tlb_batch {
     int* qstart;    // [kMaxGroups][kQueues + 1]
     int* counters;  // [kMaxGroups][2][kQueues]
     int nitems;
+    // Two-step launches, in a launch shape of their own: used unless the caller has set a shape (or the tuner
+    // found single steps faster).  Single steps between them (odd counts) keep a queue parity of their own.
+    bool pairs;
+    std::vector<int> pair_cols, pair_chunk;  // per domain: columns and rows of an item
+    int2* pair_items;
+    int pair_grid;
+    int single_parity;
     void* fields;
     double* staging;
     double* diag_partial;
@@ -436,6 +476,78 @@ static hipError_t sync_groups(tlb_batch* b)
     return e;
 }
 
+// Items of the two-step launches, made once: they depend on the domains alone.  An item of c rows takes c + 7
+// iterations, so longer items cost less in all and more at the end, where the last of them run alone.  The
+// rows are those that end first when every queue's items are dealt in order to the items its XCD holds at
+// once (four per compute unit).  512 domains of 32 to 256 nodes a side, FP32: 356 us per step at 38 rows,
+// 364 at 55, 409 at 110; 16 domains of up to 128: 9.7 us at 4 rows, 11.8 at 8.
+static tlb_status build_pairs(tlb_batch* b)
+{
+    constexpr int kCols = 58, kFill = 7;
+    int dev = 0, ncu = 0;
+    BHIP(hipGetDevice(&dev));
+    BHIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    const int slots = std::max(1, 4 * ncu / kQueues);
+    std::vector<int> order(b->ndom);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
+        return (int64_t)b->p[a].nx * b->p[a].ny > (int64_t)b->p[c].nx * b->p[c].ny;
+    });
+    auto strips = [&](int d) { return (b->p[d].nx + kCols - 1) / kCols; };
+    auto rows = [&](int d, int target) {
+        const int n = std::max(1, (b->p[d].ny + target / 2) / target);
+        return (b->p[d].ny + n - 1) / n;
+    };
+    // domains to the least-loaded queue, in decreasing size
+    auto deal = [&](int target, auto item) {
+        std::vector<int64_t> load(kQueues, 0);
+        for (int d : order) {
+            const int c = rows(d, target), n = (b->p[d].ny + c - 1) / c, ntx = strips(d);
+            const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+            load[k] += (int64_t)ntx * n * (c + kFill);
+            for (int i = 0; i < n; ++i)
+                for (int s = 0; s < ntx; ++s) item(k, d, s, i, std::min(c, b->p[d].ny - i * c) + kFill);
+        }
+    };
+    int best_target = 4;
+    int64_t best_end = INT64_MAX;
+    for (int target : {2, 4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40, 48, 56, 64, 80, 96, 128, 192, 256}) {
+        std::vector<std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>>> free_at(kQueues);
+        int64_t end = 0;
+        deal(target, [&](int k, int, int, int, int time) {
+            int64_t t = 0;
+            if ((int)free_at[k].size() >= slots) {
+                t = free_at[k].top();
+                free_at[k].pop();
+            }
+            free_at[k].push(t + time);
+            end = std::max(end, t + time);
+        });
+        if (end < best_end) {
+            best_end = end;
+            best_target = target;
+        }
+    }
+    b->pair_cols.resize(b->ndom);
+    b->pair_chunk.resize(b->ndom);
+    for (int d = 0; d < b->ndom; ++d) {
+        b->pair_cols[d] = (b->p[d].nx + strips(d) - 1) / strips(d);
+        b->pair_chunk[d] = rows(d, best_target);
+    }
+    std::vector<std::vector<int2>> q(kQueues);
+    deal(best_target, [&](int k, int d, int s, int i, int) { q[k].push_back(make_int2(d, (s << 16) | i)); });
+    size_t most = 0;
+    for (const auto& v : q) most = std::max(most, v.size());
+    std::vector<int2> items(most * kQueues, make_int2(-1, 0));
+    for (int k = 0; k < kQueues; ++k)
+        for (size_t i = 0; i < q[k].size(); ++i) items[i * kQueues + k] = q[k][i];
+    BHIP(hipMalloc((void**)&b->pair_items, sizeof(int2) * items.size()));
+    BHIP(hipMemcpyAsync(b->pair_items, items.data(), sizeof(int2) * items.size(), hipMemcpyHostToDevice, b->stream));
+    BHIP(hipStreamSynchronize(b->stream));
+    b->pair_grid = (int)items.size();
+    return TLB_OK;
+}
+
 // Work items and queues for the current launch shape: domains go to the
 // least-loaded stream group in decreasing size, then, within a group, to its
 // least-loaded queue in decreasing size; within a queue, larger domains come
@@ -482,6 +594,8 @@ static tlb_status build_items(tlb_batch* b)
             D.ny = p.ny;
             D.walls = p.walls_y;
             D.P = phys_of<acc_t<T>>(p);
+            D.pair_cols = b->pair_cols[d];
+            D.pair_chunk = b->pair_chunk[d];
             const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
             if (b->launch.variant == 2 && p.nx + 3 <= W) {
                 // flat sweep: items of `rows` segments of W positions of the padded rows
@@ -537,6 +651,7 @@ static tlb_status build_items(tlb_batch* b)
         qs[(size_t)L * (kQueues + 1) + kQueues] = (int)items.size();
         group_items[L] = (int)items.size() - first;
     }
+    b->single_parity = 0;
     if (b->items) BHIP(hipFree(b->items));
     b->items = nullptr;
     BHIP(hipMalloc((void**)&b->items, sizeof(int2) * items.size()));
@@ -619,6 +734,7 @@ extern "C" tlb_status tlb_batch_create(const tlb_params* per_dom, int32_t ndom, 
     b->launch.chunk = 16;
     b->launch.variant = prec == TLB_F32 ? 1 : 0;
     b->groups = 1;
+    b->pairs = true;
     hipError_t e = hipSuccess;
     if (stream) {
         b->stream = (hipStream_t)stream;
@@ -643,7 +759,8 @@ extern "C" tlb_status tlb_batch_create(const tlb_params* per_dom, int32_t ndom, 
         tlb_batch_destroy(b);
         return e == hipErrorOutOfMemory ? TLB_ENOMEM : TLB_EHIP;
     }
-    tlb_status st = rebuild(b);
+    tlb_status st = build_pairs(b);
+    if (!st) st = rebuild(b);
     if (st) {
         tlb_batch_destroy(b);
         return st;
@@ -657,7 +774,7 @@ extern "C" tlb_status tlb_batch_destroy(tlb_batch* b)
     if (!b) return TLB_EINVAL;
     (void)sync_groups(b);
     drop_graph(b);
-    for (void* ptr : {b->state[0], b->state[1], b->wet, b->doms, (void*)b->items, (void*)b->qstart, (void*)b->counters,
+    for (void* ptr : {b->state[0], b->state[1], b->wet, b->doms, (void*)b->items, (void*)b->pair_items, (void*)b->qstart, (void*)b->counters,
                       b->fields, (void*)b->staging, (void*)b->diag_partial, (void*)b->diag_out})
         if (ptr) (void)hipFree(ptr);
     for (int L = 0; L < kMaxGroups; ++L) {
@@ -764,7 +881,7 @@ static hipStream_t gstream(const tlb_batch* b, int L) { return b->groups > 1 ? b
 
 // One step of stream group L from buffer `cur` on the group's stream.
 template <typename T>
-static tlb_status batch_launch_one(tlb_batch* b, int L, int cur)
+static tlb_status batch_launch_one(tlb_batch* b, int L, int cur, int parity)
 {
     BatchArgs<T> a;
     a.src = (const T*)b->state[cur];
@@ -774,14 +891,35 @@ static tlb_status batch_launch_one(tlb_batch* b, int L, int cur)
     a.items = b->items;
     a.qstart = b->qstart + L * (kQueues + 1);
     a.counters = b->counters + L * 2 * kQueues;
-    a.parity = cur;
+    a.parity = parity;
     BHIP(launch_batch2d<T>(a, b->launch.width, b->launch.variant, b->grid[L], gstream(b, L)));
     return TLB_OK;
 }
 
-static tlb_status launch_one(tlb_batch* b, int L, int cur)
+static tlb_status launch_one(tlb_batch* b, int L, int cur, int parity)
 {
-    return b->prec == TLB_F32 ? batch_launch_one<float>(b, L, cur) : batch_launch_one<double>(b, L, cur);
+    return b->prec == TLB_F32 ? batch_launch_one<float>(b, L, cur, parity) : batch_launch_one<double>(b, L, cur, parity);
+}
+
+// Two steps of every domain from buffer `cur`, on `stream`.
+template <typename T>
+static tlb_status batch_launch_pair(tlb_batch* b, int cur)
+{
+    BatchArgs<T> a = {};
+    a.src = (const T*)b->state[cur];
+    a.dst = (T*)b->state[cur ^ 1];
+    a.wet = (const T*)b->wet;
+    a.doms = (const DomDesc<T>*)b->doms;
+    a.items = b->pair_items;
+    a.parity = cur;  // every other launch sweeps each item the other way
+    hipLaunchKernelGGL((k_batch_pair2d<T>), dim3(b->pair_grid), dim3(128), 0, b->stream, a);
+    BHIP(hipGetLastError());
+    return TLB_OK;
+}
+
+static tlb_status launch_pair(tlb_batch* b, int cur)
+{
+    return b->prec == TLB_F32 ? batch_launch_pair<float>(b, cur) : batch_launch_pair<double>(b, cur);
 }
 
 // The groups' streams wait for the work queued on `stream` so far.
@@ -809,12 +947,56 @@ static tlb_status launch_steps(tlb_batch* b, int64_t n)
 {
     for (int64_t t = 0; t < n; ++t) {
         for (int L = 0; L < b->groups; ++L) {
-            tlb_status st = launch_one(b, L, b->cur);
+            tlb_status st = launch_one(b, L, b->cur, b->pairs ? b->single_parity : b->cur);
             if (st) return st;
         }
         b->cur ^= 1;
+        b->single_parity ^= 1;
     }
     return TLB_OK;
+}
+
+// nsteps steps, two to a launch: whole chains of launches from the captured graph (an even number of them,
+// from buffer 0 back to it: graph_steps steps, or twice as many), the rest directly.
+static tlb_status step_pairs(tlb_batch* b, int64_t nsteps)
+{
+    tlb_status st = TLB_OK;
+    const int64_t chain = b->graph_steps % 4 == 0 ? b->graph_steps : 2 * (int64_t)b->graph_steps;
+    if (chain > 0 && nsteps >= chain + (b->cur != 0 ? 2 : 0)) {
+        if (b->cur != 0) {
+            st = launch_pair(b, b->cur);
+            if (st) return st;
+            b->cur ^= 1;
+            nsteps -= 2;
+        }
+        if (!b->graph_exec[0]) {
+            if (b->graph[0]) (void)hipGraphDestroy(b->graph[0]);
+            b->graph[0] = nullptr;
+            BHIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
+            for (int64_t t = 0; t < chain / 2 && !st; ++t) st = launch_pair(b, (int)(t & 1));
+            hipGraph_t g = nullptr;
+            const hipError_t e = hipStreamEndCapture(b->stream, &g);
+            if (st) {
+                if (g) (void)hipGraphDestroy(g);
+                return st;
+            }
+            BHIP(e);
+            b->graph[0] = g;
+            BHIP(hipGraphInstantiate(&b->graph_exec[0], g, nullptr, nullptr, 0));
+        }
+        for (; nsteps >= chain; nsteps -= chain) BHIP(hipGraphLaunch(b->graph_exec[0], b->stream));
+    }
+    for (; nsteps >= 2; nsteps -= 2) {
+        st = launch_pair(b, b->cur);
+        if (st) return st;
+        b->cur ^= 1;
+    }
+    if (nsteps > 0) {
+        st = fork_groups(b);
+        if (!st) st = launch_steps(b, nsteps);
+        if (!st) st = join_groups(b);
+    }
+    return st;
 }
 
 static tlb_status batch_direct(tlb_batch* b, int64_t n)
@@ -830,7 +1012,13 @@ extern "C" tlb_status tlb_batch_step(tlb_batch* b, int64_t nsteps)
     if (!b || nsteps < 0) return TLB_EINVAL;
     if (!b->ready) return TLB_ESTATE;
     int64_t left = nsteps;
-    tlb_status st = fork_groups(b);
+    tlb_status st = TLB_OK;
+    if (b->pairs) {
+        st = step_pairs(b, nsteps);
+        if (!st) b->step += nsteps;
+        return st;
+    }
+    st = fork_groups(b);
     if (st) return st;
     if (b->graph_steps > 0 && left >= b->graph_steps) {
         if (b->cur != 0) {  // the captured chains start from buffer 0
@@ -843,7 +1031,7 @@ extern "C" tlb_status tlb_batch_step(tlb_batch* b, int64_t nsteps)
             if (b->graph_exec[L]) continue;
             hipStream_t s = gstream(b, L);
             BHIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-            for (int t = 0; t < b->graph_steps && !st; ++t) st = launch_one(b, L, t & 1);
+            for (int t = 0; t < b->graph_steps && !st; ++t) st = launch_one(b, L, t & 1, t & 1);
             hipGraph_t g = nullptr;
             hipError_t e = hipStreamEndCapture(s, &g);
             if (st) return st;
@@ -884,6 +1072,7 @@ extern "C" tlb_status tlb_batch_set_launch(tlb_batch* b, const tlb_launch* l)
     b->launch = *l;
     b->groups = std::max(1, std::min(l->height, b->ndom));
     b->launch.height = b->groups;
+    b->pairs = false;
     const tlb_status st = rebuild(b);
     if (st) {  // keep the batch steppable in its previous shape
         b->launch = old;
@@ -1020,6 +1209,7 @@ extern "C" tlb_status tlb_batch_autotune(tlb_batch* b, int32_t trial_steps, tlb_
     if (cache && cache_lookup(cache, key, &best)) {
         tlb_status st = tlb_batch_set_launch(b, &best);
         if (st) return st;
+        b->pairs = true;
         if (chosen) *chosen = best;
         return TLB_OK;
     }
@@ -1069,6 +1259,19 @@ extern "C" tlb_status tlb_batch_autotune(tlb_batch* b, int32_t trial_steps, tlb_
     for (int g = 1; g <= std::min(kMaxGroups, b->ndom) && !st; ++g)
         for (int f = 1; f <= 4 && !st; f *= 2)
             if ((int64_t)one.chunk * f <= 65535) trial(tlb_launch{one.width, g, one.chunk * f, one.variant}, 4 * trial_steps);
+    // two steps per launch against the fastest of them, over the same steps
+    bool pairs = false;
+    if (!st) {
+        const int64_t n = std::max<int64_t>(2, 4 * (int64_t)trial_steps / 2 * 2);
+        st = step_pairs(b, n);
+        (void)hipEventRecord(e0, b->stream);
+        if (!st) st = step_pairs(b, n);
+        (void)hipEventRecord(e1, b->stream);
+        (void)hipEventSynchronize(e1);
+        float ms = 0;
+        (void)hipEventElapsedTime(&ms, e0, e1);
+        pairs = !st && ms / (float)n < best_ms / (float)(4 * (int64_t)trial_steps);
+    }
     (void)hipMemcpyAsync(b->state[cur0], save, bytes, hipMemcpyDeviceToDevice, b->stream);
     (void)hipStreamSynchronize(b->stream);
     (void)hipFree(save);
@@ -1079,6 +1282,7 @@ extern "C" tlb_status tlb_batch_autotune(tlb_batch* b, int32_t trial_steps, tlb_
     if (st) return st;
     st = tlb_batch_set_launch(b, &best);
     if (st) return st;
+    b->pairs = pairs;
     if (cache) {
         FILE* f = fopen(cache, "a");
         if (f) {

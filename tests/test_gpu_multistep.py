@@ -84,3 +84,46 @@ def test_checks_between_odd_counts():
     two.step(11)
     one.step(11)
     assert np.array_equal(two.all_populations(), one.all_populations())
+
+
+@pytest.mark.parametrize("walls", [0, 1])
+@pytest.mark.parametrize("chain", [0, 4, 6])
+def test_batch_two_steps_per_launch(walls, chain):
+    """A batch in its default (two steps per launch) against single steps of its domains: strips of one and
+    several, chunks of one and several, odd counts (a single step between launches of two), captured chains
+    of an odd and an even number of launches, and again after the tuner."""
+    from paper_1511_02155_amd import tlb
+
+    sizes = [(3, 3), (5, 70), (58, 9), (59, 31), (116, 64), (117, 200), (256, 33), (64, 256)]
+    for prec in (tlb.TLB_F32, tlb.TLB_F64):
+        rng = np.random.default_rng(chain + walls)
+        ps, sims = [], []
+        for d, (nx, ny) in enumerate(sizes):
+            ps.append(tlb.make_params(0, nx, ny, prec=prec, walls_y=walls, kappa=rng.uniform(0.005, 0.03, 3), tau_f=0.8,
+                                      tau_g=0.9, tau_k=1.1, gamma_phi=0.4, gamma_psi=0.13))
+        b = tlb.Batch(ps)
+        for d, (nx, ny) in enumerate(sizes):
+            s = tlb.Sim(ps[d])
+            s.set_launch(**s.launch())
+            C = 1.0 / 3.0 + rng.uniform(-0.05, 0.05, (3, nx * ny))
+            u = rng.uniform(-0.02, 0.02, (2, nx * ny))
+            if walls:
+                h = rng.uniform(-0.001, 0.001, (2, 3, nx))
+                s.set_wetting_both(h)
+                for w in (0, 1):
+                    b.set_wetting(d, w, h[w])
+            s.init_equilibrium(C, u)
+            b.init_equilibrium(d, C, u)
+            sims.append(s)
+        if chain:
+            b.set_graph(chain)
+        for n in (1, 2, 3, 2 * chain + 5, 4 * chain + 2):
+            b.step(n)
+            for d, s in enumerate(sims):
+                s.step(n)
+                assert np.array_equal(b.all_populations(d), s.all_populations())
+        b.autotune(2)
+        b.step(2 * chain + 3)
+        for d, s in enumerate(sims):
+            s.step(2 * chain + 3)
+            assert np.array_equal(b.all_populations(d), s.all_populations())
