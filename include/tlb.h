@@ -401,7 +401,7 @@ tlb_status tlb_set_wetting_dev(tlb_sim* sim, int wall, const void* h_dev);
  *   D2Q9: each workgroup sweeps a strip of `width` columns (64, 128 or 256)
  *     over `chunk` rows; variant 1 prefetches the next row's populations while
  *     the current row is collided, variant 0 does not.  Until a shape is set with
- *     tlb_set_launch, tlb_step advances lattices of at most 4 GiB two or three
+ *     tlb_set_launch, tlb_step advances lattices of at most 4 GiB two to four
  *     steps per launch where that is faster, in shapes of its own, with bitwise
  *     the same results; a shape set here is used for every step.
  *   D3Q19: each workgroup sweeps a tile of width x height columns (32x8 or

@@ -581,8 +581,9 @@ static hipError_t launch_one(const tlb_sim* s, const StepArgs<T>& a)
                                   s->p.collision == TLB_MRT, s->nc, s->stream);
 }
 
-// How a launch advances a D2Q9 lattice: one step (the strip kernel), two in sweeps or two or three in tiles.
-enum class Way { one, pair, tile };
+// How a launch advances a D2Q9 lattice: one step (the strip kernel), two or four in sweeps, or two or three in
+// tiles.
+enum class Way { one, pair, four, tile };
 
 // n steps launched directly, several to a launch where that is faster: D2Q9 in the default launch, a state
 // of one buffer descriptor.  even: in an even number of launches (n is even), so that the state ends in the
@@ -591,10 +592,10 @@ template <typename T>
 static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
 {
     const StepArgs<T> one = step_args<T>(s);
-    StepArgs<T> pair = one;
+    StepArgs<T> pair = one, four = one;
     Way way = Way::one;
     int tile = -1, tile_two = -1, steps = 1;
-    // the way for two steps left over by launches of three
+    // the way for two steps left over by launches of three or four
     Way two = Way::tile;
     if (n > 1 && s->p.lattice == TLB_D2Q9 && !s->launch_set && tlb_state_bytes(s) <= (int64_t)0xFFFFFF00) {
         // Times per step in us.  The strip kernel's items of several rows are never the fastest; with one row
@@ -604,11 +605,19 @@ static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
         double best = s->launch.chunk > 1 ? 1e300
                       : s->nc > 3         ? (waves <= 600.0 ? 8.7 + 0.0015 * waves : 12.5)
                                           : 7.0 + 0.0016 * waves;
-        const double tp = pair2d_shape<T>(pair, s->nc, s->cus);
+        const double tp = pair2d_shape<T>(pair, s->nc, s->cus, 2);
         if (tp < best) {
             best = tp;
             way = Way::pair;
             steps = 2;
+        }
+        if (s->p.prec == TLB_F64 && s->nc <= 4 && n >= 4) {
+            const double t4 = pair2d_shape<T>(four, s->nc, s->cus, 4);
+            if (t4 < best) {
+                best = t4;
+                way = Way::four;
+                steps = 4;
+            }
         }
         const bool f64 = s->p.prec == TLB_F64;
         double tt = 0.0, t2 = 0.0;
@@ -622,19 +631,20 @@ static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
     }
     const bool mrt = s->p.collision == TLB_MRT;
     auto go = [&](Way w, int shape) {
-        StepArgs<T> a = w == Way::pair ? pair : one;
+        StepArgs<T> a = w == Way::pair ? pair : w == Way::four ? four : one;
         a.src = (const T*)s->state[s->cur];
         a.dst = (T*)s->state[s->cur ^ 1];
         a.flip = s->cur;  // every other launch sweeps each chunk the other way
         s->cur ^= 1;
-        return w == Way::pair   ? launch_pair2d<T>(a, mrt, s->nc, s->stream)
+        return w == Way::pair   ? launch_pair2d<T>(a, 2, mrt, s->nc, s->stream)
+               : w == Way::four ? launch_pair2d<T>(a, 4, mrt, s->nc, s->stream)
                : w == Way::tile ? launch_tile2d<T>(a, shape, mrt, s->nc, s->stream)
                                 : launch_one<T>(s, a);
     };
     int64_t many = n / steps, twos = 0, ones = n % steps;
-    if (ones == 2) {  // left over by launches of three
+    if (ones >= 2) {  // left over by launches of three or four
         twos = 1;
-        ones = 0;
+        ones -= 2;
     }
     if (even && ((many + twos + ones) & 1)) {
         if (twos > 0) {  // two steps one by one
@@ -644,6 +654,9 @@ static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
             --many;
             ++twos;
             ++ones;
+        } else if (steps == 4) {  // four as two and two
+            --many;
+            twos += 2;
         } else {
             --many;
             ones += 2;

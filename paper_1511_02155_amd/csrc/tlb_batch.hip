@@ -296,7 +296,7 @@ void k_batch2d(BatchArgs<T> B)
 template <typename T>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k_batch_pair2d(BatchArgs<T> B)
 {
-    __shared__ PairLds<T, 3> S;
+    __shared__ PairLds<T, 3, 2> M;
     const int2 w = B.items[blockIdx.x];
     if (w.x < 0) return;
     const DomDesc<T>& D = B.doms[w.x];
@@ -313,9 +313,9 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int x0 = strip * D.pair_cols, ncols = min(D.pair_cols, D.nx - x0);
     const int y0 = chunk * D.pair_chunk, L = min(D.pair_chunk, D.ny - y0);
     if (((chunk ^ B.parity) & 1) == 0)
-        pair_sweep<T, 1, false, 3>(A, x0, ncols, y0, L, S);
+        pair_sweep<T, 1, false, 3, 2>(A, x0, ncols, y0, L, M);
     else
-        pair_sweep<T, -1, false, 3>(A, x0, ncols, y0, L, S);
+        pair_sweep<T, -1, false, 3, 2>(A, x0, ncols, y0, L, M);
 }
 
 template <typename T>
@@ -483,7 +483,7 @@ static hipError_t sync_groups(tlb_batch* b)
 // 364 at 55, 409 at 110; 16 domains of up to 128: 9.7 us at 4 rows, 11.8 at 8.
 static tlb_status build_pairs(tlb_batch* b)
 {
-    constexpr int kCols = 58, kFill = 7;
+    constexpr int kCols = pair_cols(2), kFill = pair_fill(2);
     int dev = 0, ncu = 0;
     BHIP(hipGetDevice(&dev));
     BHIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));

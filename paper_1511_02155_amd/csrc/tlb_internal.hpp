@@ -39,12 +39,12 @@ __device__ __forceinline__ int xcd_item(int b, int G)
 
 template <typename T>
 hipError_t launch_step2d(const StepArgs<T>& a, int width, int hold, bool mrt, int nc, hipStream_t s);
-// Two D2Q9 steps in one launch (tlb_pair2d.hip), and its strips and chunks for the lattice of `a`;
-// returns its time per step in us.
+// Two D2Q9 steps in one launch, or four in FP64 of three or four components (tlb_pair2d.hip), and the strips and
+// chunks for the lattice of `a`; returns the time per step in us.
 template <typename T>
-double pair2d_shape(StepArgs<T>& a, int nc, int cus);
+double pair2d_shape(StepArgs<T>& a, int nc, int cus, int steps);
 template <typename T>
-hipError_t launch_pair2d(const StepArgs<T>& a, bool mrt, int nc, hipStream_t s);
+hipError_t launch_pair2d(const StepArgs<T>& a, int steps, bool mrt, int nc, hipStream_t s);
 // Two or three D2Q9 steps in one launch, in tiles (tlb_tile2d.hip): the best tiles for a lattice (of `steps`
 // steps where steps != 0) and their time per step, the steps of a shape, the launch.
 int tile2d_best(int nx, int ny, int nc, bool f64, int cus, int steps, double* us);

@@ -1,10 +1,10 @@
 """Launches of several D2Q9 steps (tlb_pair2d.hip, tlb_tile2d.hip) against single steps.
 
-With the default launch shape tlb_step advances D2Q9 lattices two or three steps per launch; with a launch
+With the default launch shape tlb_step advances D2Q9 lattices two to four steps per launch; with a launch
 shape set by the caller every step is a launch of the one-step kernel.  All form every value by the same
 operations in the same order, so the results are the same bit for bit (tolerance zero).  The small sizes sit
 at the edges of the tiles (8 x 4, 16 x 8, 12 x 8 and 32 x 8 nodes, each the default of one of the sizes), the
-large ones at those of the sweeps' strips (58 columns) and chunks.
+large ones at those of the sweeps' strips (58 columns for two steps, 50 for four) and chunks.
 """
 import numpy as np
 import pytest
@@ -46,7 +46,7 @@ def test_launches_of_several_steps_equal_single_steps(size, walls, nc, mrt):
             assert np.array_equal(two.all_populations(), one.all_populations())
 
 
-@pytest.mark.parametrize("size", [(1045, 800), (1500, 1100)], ids=lambda s: "%dx%d" % s)
+@pytest.mark.parametrize("size", [(1045, 800), (1501, 1100)], ids=lambda s: "%dx%d" % s)
 @pytest.mark.parametrize("walls,nc,mrt", [(0, 3, 0), (1, 3, 0), (1, 3, 1), (1, 4, 0), (0, 4, 1), (1, 5, 1), (0, 5, 0)])
 def test_sweeps_of_many_chunks_and_rounds(size, walls, nc, mrt):
     """Chunks of several rows, strips of 57 and 58 columns, more items than the chip holds at once, both sweep
@@ -55,13 +55,14 @@ def test_sweeps_of_many_chunks_and_rounds(size, walls, nc, mrt):
 
     for prec in (tlb.TLB_F32, tlb.TLB_F64):
         two, one = _pair(tlb, *size, prec, walls, nc, mrt)
-        two.step(5)
-        one.step(5)
-        for s in (0, nc - 1):
-            assert np.array_equal(two.populations(s), one.populations(s))
+        for n in (5, 6, 3):  # launches of four and what they leave over
+            two.step(n)
+            one.step(n)
+            for s in (0, nc - 1):
+                assert np.array_equal(two.populations(s), one.populations(s))
 
 
-@pytest.mark.parametrize("size", [(90, 50), (333, 217)], ids=lambda s: "%dx%d" % s)
+@pytest.mark.parametrize("size", [(90, 50), (333, 217), (1045, 800)], ids=lambda s: "%dx%d" % s)
 @pytest.mark.parametrize("chain", [2, 4, 6, 8, 10])
 def test_captured_chains(chain, size):
     """Chains of an odd or even number of launches, replayed several times with eager work between."""
