@@ -48,6 +48,7 @@ struct tlb_sim {
     int64_t check_every;
     tlb_launch launch;
     bool launch_set;          // the launch shape is the caller's: every step runs in exactly that shape
+    int tile_bx, tile_by, tile_chunk;  // D3Q19: tile of the default launch where no compiled-in one fits (bx > 0)
     double* hhost;            // [2][nc][nx*nz] h_m as last set from the host (range report)
     int64_t wet_outside[2];   // per wall: values with |4 h_m / (alpha kappa_m)| > 1, -1 if set from device memory
     bool wet_warned;
@@ -239,26 +240,49 @@ static void default_launch(tlb_sim* s)
         // worth).  The shape is the one with the smallest rounds * (chunk + 3): a few items more than
         // the chip holds cost a second, nearly empty round (96^3 FP32: 288 items 176 us per step, 252
         // items 116 us; 160^3 with several relaxation times: 300 items 774 us, 240 items 481 us).  A
-        // plane of a 32 x 8 tile takes 1.1 to 1.25 times a 64 x 4 tile's (its rows are shorter runs of
-        // memory), so the narrow tile is for lattices that leave wide ones idle; and several rounds
-        // cost about 1.2 times their planes (200^3: 200 items of all planes 1224 us, 1000 of 40 planes
-        // 1361 us), the starts of the later ones among them.
+        // plane takes the longer the shorter the tile's rows, about as 1 + 16/width in FP32 (32 x 8
+        // against 64 x 4: 1.1 to 1.25 times) and 1 + 12/width in FP64; several rounds cost about 1.2
+        // times their planes (200^3: 200 items of all planes 1224 us, 1000 of 40 planes 1361 us).
         const int slots = s->cus > 0 ? s->cus : 256;
-        double best = 1e300;
-        for (int bx : {64, 32}) {
-            const int by = 256 / bx;
+        const double narrow = p.prec == TLB_F32 ? 16.0 : 12.0;
+        auto shape = [&](int bx, int by, double& best, int& chunk) {
             const int64_t tiles = (int64_t)((p.nx + bx - 1) / bx) * ((p.ny + by - 1) / by);
+            bool better = false;
             for (int64_t rounds = 1; rounds <= 64; ++rounds) {
                 const int64_t nch = std::min<int64_t>(p.nz, std::max<int64_t>(1, rounds * slots / tiles));
-                const int chunk = (int)((p.nz + nch - 1) / nch);
-                const int64_t items = tiles * ((p.nz + chunk - 1) / chunk);
+                const int c = (int)((p.nz + nch - 1) / nch);
+                const int64_t items = tiles * ((p.nz + c - 1) / c);
                 const int64_t turns = (items + slots - 1) / slots;
-                const double cost = (double)turns * (chunk + 3) * (bx == 32 ? 1.2 : 1.0) * (turns > 1 ? 1.2 : 1.0);
+                double cost = (double)turns * (c + 3) * (1.0 + narrow / bx) * (turns > 1 ? 1.2 : 1.0);
+                if (bx == p.nx) cost *= p.prec == TLB_F32 ? 0.93 : 0.97;  // whole rows: no ring columns of other tiles
                 if (cost < best) {
                     best = cost;
-                    s->launch.width = bx;
-                    s->launch.height = by;
-                    s->launch.chunk = chunk;
+                    chunk = c;
+                    better = true;
+                }
+            }
+            return better;
+        };
+        double best = 1e300;
+        for (int bx : {64, 32})
+            if (shape(bx, 256 / bx, best, s->launch.chunk)) {
+                s->launch.width = bx;
+                s->launch.height = 256 / bx;
+            }
+        // Tiles of run-time size, whose rows divide the lattice's, where they promise 8% and more (FP64
+        // 11%; 17 x 121 x 26 FP64 in 17 x 15 lost 9% where the rule promised 8): 70 x 50 x 45 FP64 50 us
+        // per step in 70 x 3 tiles, 58 in 64 x 4; 67 x 74 x 89 FP32 56 in 67 x 3, 70 in 64 x 4;
+        // 42 x 148 x 106 FP32, several relaxation times, 99 in 42 x 6, 130 in 64 x 4.
+        s->tile_bx = 0;
+        best *= p.prec == TLB_F32 ? 0.92 : 0.89;
+        for (int k = 1; (p.nx + k - 1) / k >= 12; ++k) {
+            const int bx = (p.nx + k - 1) / k;
+            if (bx > kTileWide) continue;
+            for (int by = std::min(256 / bx, p.ny); by >= 2; --by) {
+                if (2 * (bx + 2) + 2 * by > 256) continue;  // a lane for every ring node
+                if (shape(bx, by, best, s->tile_chunk)) {
+                    s->tile_bx = bx;
+                    s->tile_by = by;
                 }
             }
         }
@@ -571,6 +595,23 @@ static StepArgs<T> step_args(const tlb_sim* s)
     return a;
 }
 
+// The arguments of a step in the default launch: D3Q19 may have a tile of its own.
+template <typename T>
+static StepArgs<T> own_args(const tlb_sim* s)
+{
+    StepArgs<T> a = step_args<T>(s);
+    if (s->p.lattice == TLB_D3Q19 && !s->launch_set && s->tile_bx > 0) {
+        a.bx = s->tile_bx;
+        a.by = s->tile_by;
+        a.chunk = s->tile_chunk;
+        a.ntx = (s->p.nx + a.bx - 1) / a.bx;
+        a.nty = (s->p.ny + a.by - 1) / a.by;
+        a.nchunks = (s->p.nz + a.chunk - 1) / a.chunk;
+        a.nitems = a.ntx * a.nty * a.nchunks;
+    }
+    return a;
+}
+
 template <typename T>
 static hipError_t launch_one(const tlb_sim* s, const StepArgs<T>& a)
 {
@@ -591,7 +632,7 @@ enum class Way { one, pair, four, tile };
 template <typename T>
 static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
 {
-    const StepArgs<T> one = step_args<T>(s);
+    const StepArgs<T> one = own_args<T>(s);
     StepArgs<T> pair = one, four = one;
     Way way = Way::one;
     int tile = -1, tile_two = -1, steps = 1;

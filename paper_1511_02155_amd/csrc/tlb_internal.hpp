@@ -22,10 +22,14 @@ struct StepArgs {
     int ntx, nty; // strips (D2Q9: ntx) / tiles (D3Q19: ntx * nty) across the sweep
     int nitems;   // ntx * nty * nchunks
     int cols;     // D2Q9 two-step launches: columns of a strip
+    int bx, by;   // D3Q19 tiles of run-time size: columns (0: a compiled-in tile)
     int flip;     // D2Q9 strips: 1 reverses the sweep direction of every chunk (alternates per step)
     Phys<acc_t<T>> P;
     Phys<float> Pf;  // the same parameters for kernels whose arithmetic is FP32
 };
+
+// Widest D3Q19 tile of run-time size.
+constexpr int kTileWide = 128;
 
 // Map a hardware workgroup id onto a logical work item so that each XCD
 // (workgroups are dispatched round-robin over the 8 XCDs) receives a

@@ -112,14 +112,24 @@ __device__ __forceinline__ const Phys<double>& phys3d<double>(const StepArgs<dou
     return A.P;
 }
 
-template <typename T, int BX, int BY, int VAR, bool MRT, int NC, bool NT>
-__global__ __launch_bounds__(BX* BY) void k_step3d(StepArgs<T> A)
+// Nodes of a tile plane with its ring: of the compiled-in tiles, and the most of a tile of run-time size
+// (FX = 0: any width up to kTileWide of at most 256 lanes), whose rows start at run-time offsets.
+template <int FX, int FY>
+constexpr int tile3d_nodes()
+{
+    return FX > 0 ? (FX + 2) * (FY + 2) : (kTileWide + 2) * (256 / kTileWide + 2);
+}
+
+template <typename T, int FX, int FY, int VAR, bool MRT, int NC, bool NT>
+__global__ __launch_bounds__(FX > 0 ? FX * FY : 256) void k_step3d(StepArgs<T> A)
 {
     using C = T;
     constexpr int J = 19 * NC;  // populations per node
     const Phys<C>& PH = phys3d<T>(A);
     constexpr bool HOLD = VAR == 1;
-    __shared__ C lds[2][NC][BY + 2][BX + 2];
+    __shared__ C lds[2][NC][tile3d_nodes<FX, FY>()];
+    const int BX = FX > 0 ? FX : A.bx, BY = FX > 0 ? FY : A.by;
+    const int LP = BX + 2;  // LDS row
 
     const int item = xcd_item(blockIdx.x, A.nitems);
     const int tile = item / A.nchunks;
@@ -129,10 +139,12 @@ __global__ __launch_bounds__(BX* BY) void k_step3d(StepArgs<T> A)
     const int x0 = txi * BX, y0 = tyi * BY;
     const int ax = min(BX, A.nx - x0), ay = min(BY, A.ny - y0);
     const int t = threadIdx.x;
-    const int tx = t % BX, ty = t / BX;
+    const int ty = t / BX, tx = t - ty * BX;
     const bool active = tx < ax && ty < ay;
     const int x = x0 + min(tx, ax - 1);
     const int y = y0 + min(ty, ay - 1);
+    // LDS places of the lane's node and of its ring node; lanes past the tile's last row read in bounds
+    const int at = (FX > 0 ? ty + 1 : min(ty, BY - 1) + 1) * LP + tx + 1;
     const int z0 = chunk * A.chunk;
     const int z1 = min(z0 + A.chunk, A.nz);
 
@@ -201,7 +213,7 @@ __global__ __launch_bounds__(BX* BY) void k_step3d(StepArgs<T> A)
         conc_dev<C, NC>(mo, p.c);
         if (active) {
 #pragma unroll
-            for (int m = 0; m < NC; ++m) lds[buf][m][ty + 1][tx + 1] = p.c[m];
+            for (int m = 0; m < NC; ++m) lds[buf][m][at] = p.c[m];
         }
         if (ring) {
             T hf[J];
@@ -215,19 +227,19 @@ __global__ __launch_bounds__(BX* BY) void k_step3d(StepArgs<T> A)
                 for (int m = 0; m < NC; ++m) hc[m] += C(wt[m * nxz]);
             }
 #pragma unroll
-            for (int m = 0; m < NC; ++m) lds[buf][m][hy + 1][hx + 1] = hc[m];
+            for (int m = 0; m < NC; ++m) lds[buf][m][(hy + 1) * LP + hx + 1] = hc[m];
         }
         __syncthreads();
 #pragma unroll
         for (int m = 0; m < NC; ++m) {
-            const C l = lds[buf][m][ty + 1][tx];
-            const C r = lds[buf][m][ty + 1][tx + 2];
-            const C d = lds[buf][m][ty][tx + 1];
-            const C u = lds[buf][m][ty + 2][tx + 1];
-            const C ld = lds[buf][m][ty][tx];
-            const C rd = lds[buf][m][ty][tx + 2];
-            const C lu = lds[buf][m][ty + 2][tx];
-            const C ru = lds[buf][m][ty + 2][tx + 2];
+            const C l = lds[buf][m][at - 1];
+            const C r = lds[buf][m][at + 1];
+            const C d = lds[buf][m][at - LP];
+            const C u = lds[buf][m][at + LP];
+            const C ld = lds[buf][m][at - LP - 1];
+            const C rd = lds[buf][m][at - LP + 1];
+            const C lu = lds[buf][m][at + LP - 1];
+            const C ru = lds[buf][m][at + LP + 1];
             p.A[m] = (l + r) + (d + u);
             p.Dx[m] = r - l;
             p.Dy[m] = u - d;
@@ -256,7 +268,7 @@ __global__ __launch_bounds__(BX* BY) void k_step3d(StepArgs<T> A)
         conc_dev<C, NC>(mo, p.c);
         if (active) {
 #pragma unroll
-            for (int m = 0; m < NC; ++m) lds[buf][m][ty + 1][tx + 1] = p.c[m];
+            for (int m = 0; m < NC; ++m) lds[buf][m][at] = p.c[m];
         }
         if (ring) {
             Moments<C, NC> hm = moments_as<C, L19, NC>(rf, rf + 19, rf + 38);
@@ -268,19 +280,19 @@ __global__ __launch_bounds__(BX* BY) void k_step3d(StepArgs<T> A)
                 for (int m = 0; m < NC; ++m) hc[m] += C(wt[m * nxz]);
             }
 #pragma unroll
-            for (int m = 0; m < NC; ++m) lds[buf][m][hy + 1][hx + 1] = hc[m];
+            for (int m = 0; m < NC; ++m) lds[buf][m][(hy + 1) * LP + hx + 1] = hc[m];
         }
         __syncthreads();
 #pragma unroll
         for (int m = 0; m < NC; ++m) {
-            const C l = lds[buf][m][ty + 1][tx];
-            const C r = lds[buf][m][ty + 1][tx + 2];
-            const C d = lds[buf][m][ty][tx + 1];
-            const C u = lds[buf][m][ty + 2][tx + 1];
-            const C ld = lds[buf][m][ty][tx];
-            const C rd = lds[buf][m][ty][tx + 2];
-            const C lu = lds[buf][m][ty + 2][tx];
-            const C ru = lds[buf][m][ty + 2][tx + 2];
+            const C l = lds[buf][m][at - 1];
+            const C r = lds[buf][m][at + 1];
+            const C d = lds[buf][m][at - LP];
+            const C u = lds[buf][m][at + LP];
+            const C ld = lds[buf][m][at - LP - 1];
+            const C rd = lds[buf][m][at - LP + 1];
+            const C lu = lds[buf][m][at + LP - 1];
+            const C ru = lds[buf][m][at + LP + 1];
             p.A[m] = (l + r) + (d + u);
             p.Dx[m] = r - l;
             p.Dy[m] = u - d;
@@ -428,6 +440,22 @@ hipError_t launch_step3d_n(const StepArgs<T>& a, int width, int height, int vari
 {
     dim3 grid(a.nitems);
     const bool nt = stream_stores3d<T, NC>(a);
+    // run-time tiles, for the variants that are the default of a type and component count
+    constexpr int DV = sizeof(T) == 4 ? (NC <= 4 ? 2 : 1) : (NC > 3 ? 0 : 1);
+    if (a.bx > 0 && variant == DV) {
+        if (a.by < 1 || a.bx * a.by > 256 || 2 * (a.bx + 2) + 2 * a.by > 256 || (a.bx + 2) * (a.by + 2) > tile3d_nodes<0, 0>())
+            return hipErrorInvalidValue;
+#define TLB_R3(M, N)                                                                                      \
+    if (mrt == M && nt == N) {                                                                            \
+        hipLaunchKernelGGL((k_step3d<T, 0, 0, DV, M, NC, N>), grid, dim3(256), 0, s, a);                  \
+        return hipGetLastError();                                                                         \
+    }
+        TLB_R3(false, false)
+        TLB_R3(false, true)
+        TLB_R3(true, false)
+        TLB_R3(true, true)
+#undef TLB_R3
+    }
 #define TLB_L3(BX, BY, V, M)                                                                         \
     if (width == BX && height == BY && variant == V && mrt == M) {                                   \
         if (nt)                                                                                      \
