@@ -8,6 +8,14 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(scope="module", autouse=True)
+def torch_first():
+    """torch finds the GPU only where it starts before the library does: later test files need it."""
+    import torch
+
+    torch.cuda.init()
+
 E2 = np.array([(0, 0, 0), (1, 0, 0), (-1, 0, 0), (0, 1, 0), (0, -1, 0), (1, 1, 0), (1, -1, 0), (-1, 1, 0), (-1, -1, 0)])
 E3 = np.array([(0, 0, 0), (1, 0, 0), (-1, 0, 0), (0, 1, 0), (0, -1, 0), (0, 0, 1), (0, 0, -1), (1, 1, 0), (1, -1, 0),
                (-1, 1, 0), (-1, -1, 0), (0, 1, 1), (0, 1, -1), (0, -1, 1), (0, -1, -1), (1, 0, 1), (1, 0, -1),
@@ -39,3 +47,26 @@ def test_field_rows(size, walls, nc):
             want[name] = (E[:, a, None] * p[0]).sum(0) / rho
         for name, w in want.items():
             assert np.abs(s.field(name) - w).max() <= tol, name
+
+
+def test_batch_fields_read_many_times():
+    """The first fields of a batch come through device memory, later ones through pinned host memory: both are the
+    single lattice's bit for bit (tolerance zero), also after further steps and between domains of unlike size."""
+    from paper_1511_02155_amd import tlb
+
+    sizes = [(3, 3), (65, 13), (130, 70)]
+    for prec in (tlb.TLB_F64, tlb.TLB_F32):
+        ps = [tlb.make_params(0, nx, ny, prec=prec, walls_y=1) for nx, ny in sizes]
+        b = tlb.Batch(ps)
+        sims = [tlb.Sim(p) for p in ps]
+        for d, (nx, ny) in enumerate(sizes):
+            C = 1.0 / 3 + np.random.default_rng(d).uniform(-0.05, 0.05, (3, nx * ny))
+            b.init_equilibrium(d, C)
+            sims[d].init_equilibrium(C)
+        for turn in range(3):  # 30 fields a turn
+            b.step(2)
+            for s in sims:
+                s.step(2)
+            for name in tlb.FIELDS:
+                for d, s in enumerate(sims):
+                    assert np.array_equal(b.field(d, name), s.field(name)), (turn, name, d)

@@ -12,6 +12,14 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def torch_first():
+    """torch finds the GPU only where it starts before the library does: later test files need it."""
+    import torch
+
+    torch.cuda.init()
+
+
 def _pair(tlb, nx, ny, prec, walls, nc, mrt):
     rng = np.random.default_rng(nx * 1000 + ny)
     C = 1.0 / nc + rng.uniform(-0.05, 0.05, (nc, nx * ny))

@@ -9,6 +9,14 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def torch_first():
+    """torch finds the GPU only where it starts before the library does: later test files need it."""
+    import torch
+
+    torch.cuda.init()
+
+
 @pytest.mark.parametrize("size", [(70, 50, 45), (47, 154, 9), (100, 12, 20), (18, 30, 60), (13, 3, 40), (124, 5, 6)],
                          ids=lambda s: "%dx%dx%d" % s)
 @pytest.mark.parametrize("walls,nc,mrt", [(0, 3, 0), (1, 3, 1), (1, 4, 0), (0, 5, 1)])
