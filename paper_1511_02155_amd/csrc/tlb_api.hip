@@ -627,10 +627,10 @@ static hipError_t launch_one(const tlb_sim* s, const StepArgs<T>& a)
 enum class Way { one, pair, four, tile };
 
 // n steps launched directly, several to a launch where that is faster: D2Q9 in the default launch, a state
-// of one buffer descriptor.  even: in an even number of launches (n is even), so that the state ends in the
-// buffer it started from.
+// of one buffer descriptor.  parity: in as many launches as steps, modulo two, so that an even run ends in
+// the buffer it started from, as a recorded one must.
 template <typename T>
-static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
+static tlb_status launch_steps(tlb_sim* s, int64_t n, bool parity)
 {
     const StepArgs<T> one = own_args<T>(s);
     StepArgs<T> pair = one, four = one;
@@ -687,7 +687,7 @@ static tlb_status launch_steps(tlb_sim* s, int64_t n, bool even = false)
         twos = 1;
         ones -= 2;
     }
-    if (even && ((many + twos + ones) & 1)) {
+    if (parity && ((many + twos + ones - n) & 1)) {
         if (twos > 0) {  // two steps one by one
             twos = 0;
             ones += 2;
@@ -717,7 +717,7 @@ static tlb_status run_steps(tlb_sim* s, int64_t n)
     const int64_t G = s->graph_steps;
     if (G > 0 && n >= G + (s->cur != 0 ? 1 : 0)) {
         if (s->cur != 0) {
-            tlb_status st = launch_steps<T>(s, 1);
+            tlb_status st = launch_steps<T>(s, 1, false);
             if (st) return st;
             --n;
         }
@@ -737,7 +737,7 @@ static tlb_status run_steps(tlb_sim* s, int64_t n)
         }
         for (; n >= G; n -= G) HIPCHK(hipGraphLaunch(s->graph_exec, s->stream));
     }
-    return launch_steps<T>(s, n);
+    return launch_steps<T>(s, n, capturing(s->stream));
 }
 
 template <typename T>

@@ -1008,7 +1008,10 @@ static tlb_status step_pairs(tlb_batch* b, int64_t nsteps)
         }
         for (; nsteps >= chain; nsteps -= chain) BHIP(hipGraphLaunch(b->graph_exec[0], b->stream));
     }
-    for (; nsteps >= 2; nsteps -= 2) {
+    // a recorded run swaps the buffers as often as single steps do, modulo two: where an odd number of pairs
+    // would not, the last of them runs as single steps
+    const int64_t singles = nsteps % 2 + (nsteps % 4 >= 2 && capturing(b->stream) ? 2 : 0);
+    for (; nsteps > singles; nsteps -= 2) {
         st = launch_pair(b, b->cur);
         if (st) return st;
         b->cur ^= 1;

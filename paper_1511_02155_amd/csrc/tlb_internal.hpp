@@ -31,6 +31,18 @@ struct StepArgs {
 // Widest D3Q19 tile of run-time size.
 constexpr int kTileWide = 128;
 
+// Whether a caller's stream capture is recording the stream.  A captured run of n steps has to use as many
+// buffer swaps as n single steps, modulo two: replayed, an even one then starts from the buffer it ended in.
+inline bool capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusActive;
+}
+
 // Map a hardware workgroup id onto a logical work item so that each XCD
 // (workgroups are dispatched round-robin over the 8 XCDs) receives a
 // contiguous range of items, which share halo rows through that XCD's L2.

@@ -136,3 +136,46 @@ def test_batch_two_steps_per_launch(walls, chain):
         for d, s in enumerate(sims):
             s.step(2 * chain + 3)
             assert np.array_equal(b.all_populations(d), s.all_populations())
+
+
+def _replays(torch, tlb, stream, step, runs):
+    """Record step(n) for each n of runs (an even sum) on the stream; replay the graphs in turn."""
+    graphs = []
+    for n in runs:
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            step(n)
+        graphs.append(g)
+    for _ in range(3):
+        with torch.cuda.stream(stream):
+            for g in graphs:
+                g.replay()
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("runs", [(2,), (4,), (6,), (10,), (1, 3), (5, 3)], ids=str)
+@pytest.mark.parametrize("size", [(64, 64), (333, 217), (1045, 800)], ids=lambda s: "%dx%d" % s)
+def test_runs_recorded_by_the_caller(size, runs):
+    """Steps captured into a caller's graph, replayed several times: a run swaps the state's buffers as often as
+    single steps would (modulo two), so that each replay goes on from where the last one ended."""
+    import torch
+
+    from paper_1511_02155_amd import tlb
+
+    nx, ny = size
+    C = 1.0 / 3.0 + np.random.default_rng(nx).uniform(-0.05, 0.05, (3, nx * ny))
+    for prec in (tlb.TLB_F32, tlb.TLB_F64):
+        stream = torch.cuda.Stream()
+        p = tlb.make_params(0, nx, ny, prec=prec)
+        a, b, s = tlb.Sim(p, stream=stream.cuda_stream), tlb.Batch([p, p], stream=stream.cuda_stream), tlb.Sim(p)
+        s.set_launch(**s.launch())
+        a.init_equilibrium(C)
+        s.init_equilibrium(C)
+        for d in (0, 1):
+            b.init_equilibrium(d, C)
+        _replays(torch, tlb, stream, a.step, runs)
+        _replays(torch, tlb, stream, b.step, runs)
+        s.step(3 * sum(runs))
+        want = s.all_populations()
+        assert np.array_equal(a.all_populations(), want)
+        assert np.array_equal(b.all_populations(1), want)
