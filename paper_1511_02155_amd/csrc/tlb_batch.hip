@@ -500,15 +500,24 @@ static tlb_status build_pairs(tlb_batch* b)
         const int n = std::max(1, (b->p[d].ny + target / 2) / target);
         return (b->p[d].ny + n - 1) / n;
     };
-    // domains to the least-loaded queue, in decreasing size
+    // domains to the least-loaded queue, in decreasing size, whole or, where one is more than half of what a queue
+    // gets, in pieces of neighbouring rows (two of 1000^2 FP32: 75 us per step; 176 whole, on two of the XCDs)
     auto deal = [&](int target, auto item) {
         std::vector<int64_t> load(kQueues, 0);
+        auto chunks = [&](int d) { return (b->p[d].ny + rows(d, target) - 1) / rows(d, target); };
+        auto work = [&](int d) { return (int64_t)strips(d) * chunks(d) * (rows(d, target) + kFill); };
+        int64_t total = 0;
+        for (int d : order) total += work(d);
         for (int d : order) {
-            const int c = rows(d, target), n = (b->p[d].ny + c - 1) / c, ntx = strips(d);
-            const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-            load[k] += (int64_t)ntx * n * (c + kFill);
-            for (int i = 0; i < n; ++i)
-                for (int s = 0; s < ntx; ++s) item(k, d, s, i, std::min(c, b->p[d].ny - i * c) + kFill);
+            const int c = rows(d, target), n = chunks(d), ntx = strips(d);
+            const int pieces = (int)std::min<int64_t>(n, (work(d) * 2 * kQueues + total - 1) / total);
+            for (int j = 0; j < pieces; ++j) {
+                const int i0 = (int)((int64_t)n * j / pieces), i1 = (int)((int64_t)n * (j + 1) / pieces);
+                const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+                load[k] += (int64_t)ntx * (i1 - i0) * (c + kFill);
+                for (int i = i0; i < i1; ++i)
+                    for (int s = 0; s < ntx; ++s) item(k, d, s, i, std::min(c, b->p[d].ny - i * c) + kFill);
+            }
         }
     };
     int best_target = 4;
@@ -1208,15 +1217,17 @@ static std::string batch_signature(const tlb_batch* b)
 }
 
 // Cache lines: key width chunk variant groups (lines with fewer fields are skipped).
-static bool cache_lookup(const char* path, const std::string& key, tlb_launch* l)
+// two: whether two steps per launch were faster than the shape (a last word on the line)
+static bool cache_lookup(const char* path, const std::string& key, tlb_launch* l, bool* two)
 {
     FILE* f = fopen(path, "r");
     if (!f) return false;
-    char line[256], k[128];
-    int w, c, v, g;
+    char line[256], k[128], word[8];
+    int w, c, v, g, n;
     bool found = false;
     while (fgets(line, sizeof(line), f))
-        if (sscanf(line, "%127s %d %d %d %d", k, &w, &c, &v, &g) == 5 && key == k) {
+        if ((n = sscanf(line, "%127s %d %d %d %d %7s", k, &w, &c, &v, &g, word)) >= 5 && key == k) {
+            *two = n == 6 && !strcmp(word, "two");
             l->width = w;
             l->height = g;
             l->chunk = c;
@@ -1234,10 +1245,11 @@ extern "C" tlb_status tlb_batch_autotune(tlb_batch* b, int32_t trial_steps, tlb_
     const char* cache = getenv("TLB_TUNE_CACHE");
     const std::string key = batch_signature(b);
     tlb_launch best;
-    if (cache && cache_lookup(cache, key, &best)) {
+    bool two = false;
+    if (cache && cache_lookup(cache, key, &best, &two)) {
         tlb_status st = tlb_batch_set_launch(b, &best);
         if (st) return st;
-        b->pairs = true;
+        b->pairs = two;
         if (chosen) *chosen = best;
         return TLB_OK;
     }
@@ -1314,7 +1326,8 @@ extern "C" tlb_status tlb_batch_autotune(tlb_batch* b, int32_t trial_steps, tlb_
     if (cache) {
         FILE* f = fopen(cache, "a");
         if (f) {
-            fprintf(f, "%s %d %d %d %d\n", key.c_str(), best.width, best.chunk, best.variant, best.height);
+            fprintf(f, "%s %d %d %d %d%s\n", key.c_str(), best.width, best.chunk, best.variant, best.height,
+                    pairs ? " two" : "");
             fclose(f);
         }
     }

@@ -179,3 +179,44 @@ def test_runs_recorded_by_the_caller(size, runs):
         want = s.all_populations()
         assert np.array_equal(a.all_populations(), want)
         assert np.array_equal(b.all_populations(1), want)
+
+
+@pytest.mark.parametrize("sizes", [[(300, 500)], [(700, 300), (40, 40)], [(200, 300)] * 9], ids=["one", "two", "nine"])
+def test_batch_of_few_large_domains(sizes):
+    """Two-step launches of domains that are dealt out in pieces, against single steps of each (tolerance zero)."""
+    from paper_1511_02155_amd import tlb
+
+    ps = [tlb.make_params(0, nx, ny, prec=tlb.TLB_F32, walls_y=1) for nx, ny in sizes]
+    b, sims = tlb.Batch(ps), [tlb.Sim(p) for p in ps]
+    for d, (nx, ny) in enumerate(sizes):
+        C = 1.0 / 3.0 + np.random.default_rng(d).uniform(-0.05, 0.05, (3, nx * ny))
+        b.init_equilibrium(d, C)
+        sims[d].set_launch(**sims[d].launch())
+        sims[d].init_equilibrium(C)
+    b.step(4)
+    for d, s in enumerate(sims):
+        s.step(4)
+        assert np.array_equal(b.all_populations(d), s.all_populations())
+
+
+def test_tuner_cache_keeps_its_choice(tmp_path, monkeypatch):
+    """A tuner's file names the single-step shape, and in a last word that two steps per launch were faster; results
+    after a lookup are those of the tuned batch, with and without that word (tolerance zero)."""
+    from paper_1511_02155_amd import tlb
+
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("TLB_TUNE_CACHE", str(path))
+    ps = [tlb.make_params(0, 64, 64, prec=tlb.TLB_F64) for _ in range(3)]
+    C = 1.0 / 3.0 + np.random.default_rng(2).uniform(-0.05, 0.05, (3, 64 * 64))
+    out = []
+    for turn in range(3):
+        if turn == 2:
+            path.write_text(path.read_text().replace(" two", ""))
+        b = tlb.Batch(ps)
+        for d in range(3):
+            b.init_equilibrium(d, C)
+        shape = b.autotune(2)
+        b.step(5)
+        out.append((shape, b.all_populations(2)))
+    for shape, pop in out[1:]:
+        assert shape == out[0][0] and np.array_equal(pop, out[0][1])
