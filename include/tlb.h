@@ -233,8 +233,9 @@ tlb_status tlb_set_check_every(tlb_sim* sim, int64_t every);
 
 /*
  * Replay the steps of tlb_step from a captured hipGraph in chains of
- * steps_per_graph steps (an even number; 0, the default, launches directly).  For small lattices, where a step takes about as long as its
- * launch, this removes most of the launch overhead.  The chain is captured on
+ * steps_per_graph steps (an even number; 0, the default, launches directly).
+ * For small lattices, where a step takes about as long as its launch, this
+ * removes most of the launch overhead.  The chain is captured on
  * the simulation's stream at the first tlb_step that needs it and replayed
  * after that; tlb_set_launch and tlb_set_kappa drop it (the launches hold the
  * shape and the coefficients), wetting parameters and states are read from
