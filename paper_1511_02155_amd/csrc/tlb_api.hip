@@ -55,6 +55,7 @@ struct tlb_sim {
     int64_t graph_steps;      // steps per captured chain (even), 0: every step launched directly
     hipGraph_t graph;         // the chain from buffer 0, captured on first use
     hipGraphExec_t graph_exec;
+    bool recorded;            // a caller's graph holds steps: every run keeps the buffers' parity (launch_steps)
 };
 
 // Drop the captured chain of steps (its launches hold the parameters and launch shape of capture time).
@@ -628,7 +629,9 @@ enum class Way { one, pair, four, tile };
 
 // n steps launched directly, several to a launch where that is faster: D2Q9 in the default launch, a state
 // of one buffer descriptor.  parity: in as many launches as steps, modulo two, so that an even run ends in
-// the buffer it started from, as a recorded one must.
+// the buffer it started from.  A recorded run needs that to go on, replayed, from where its last replay ended;
+// and so does every later run, recorded or not, so that the next replay finds the state in the buffer that the
+// recorded launches read.
 template <typename T>
 static tlb_status launch_steps(tlb_sim* s, int64_t n, bool parity)
 {
@@ -715,6 +718,7 @@ template <typename T>
 static tlb_status run_steps(tlb_sim* s, int64_t n)
 {
     const int64_t G = s->graph_steps;
+    if (!s->recorded && capturing(s->stream)) s->recorded = true;
     if (G > 0 && n >= G + (s->cur != 0 ? 1 : 0)) {
         if (s->cur != 0) {
             tlb_status st = launch_steps<T>(s, 1, false);
@@ -737,7 +741,7 @@ static tlb_status run_steps(tlb_sim* s, int64_t n)
         }
         for (; n >= G; n -= G) HIPCHK(hipGraphLaunch(s->graph_exec, s->stream));
     }
-    return launch_steps<T>(s, n, capturing(s->stream));
+    return launch_steps<T>(s, n, s->recorded);
 }
 
 template <typename T>

@@ -31,8 +31,7 @@ struct StepArgs {
 // Widest D3Q19 tile of run-time size.
 constexpr int kTileWide = 128;
 
-// Whether a caller's stream capture is recording the stream.  A captured run of n steps has to use as many
-// buffer swaps as n single steps, modulo two: replayed, an even one then starts from the buffer it ended in.
+// Whether a caller's stream capture is recording the stream.
 inline bool capturing(hipStream_t stream)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;

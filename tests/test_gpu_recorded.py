@@ -1,0 +1,65 @@
+"""Live runs between replays of work that a caller recorded into a graph of its own.
+
+A recorded launch holds the addresses of the buffers it was recorded with, so a live run of an even number of steps
+between two replays has to leave the state in the buffer where it found it, whatever number of steps its launches
+take.  Everything is compared with single steps (a launch shape set by the caller) bit for bit (tolerance zero).  The
+sizes are stepped in tiles, in sweeps of two steps and (FP64) in sweeps of four.
+"""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(64, 64), (512, 512), (1045, 800)]
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+
+    torch.cuda.init()
+    return torch
+
+
+def _sims(torch, tlb, nx, ny, prec):
+    """A simulation in its default launch on a stream of torch's, one that takes single steps, and their input."""
+    C = 1.0 / 3.0 + np.random.default_rng(nx).uniform(-0.05, 0.05, (3, nx * ny))
+    stream = torch.cuda.Stream()
+    p = tlb.make_params(0, nx, ny, prec=prec)
+    a, s = tlb.Sim(p, stream=stream.cuda_stream), tlb.Sim(p)
+    s.set_launch(**s.launch())
+    for x in (a, s):
+        x.init_equilibrium(C)
+    return stream, a, s, C
+
+
+def _record(torch, stream, work):
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        work()
+    return g
+
+
+def _replay(torch, stream, g):
+    with torch.cuda.stream(stream):
+        g.replay()
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("size", SIZES, ids=lambda s: "%dx%d" % s)
+@pytest.mark.parametrize("prec", [0, 1], ids=["f32", "f64"])
+def test_live_runs_between_replays_of_recorded_steps(torch, size, prec):
+    from paper_1511_02155_amd import tlb
+
+    stream, a, s, _ = _sims(torch, tlb, *size, prec)
+    graphs = [(n, _record(torch, stream, lambda: a.step(n))) for n in (2, 4)]
+    for live in ((), (2,), (4,), (6,), (10,), (1, 3), (5, 1)):
+        for n in live:
+            a.step(n)
+            s.step(n)
+        for n, g in graphs:
+            _replay(torch, stream, g)
+            s.step(n)
+        assert np.array_equal(a.field("C2"), s.field("C2")), live
+        assert np.array_equal(a.all_populations(), s.all_populations()), live
