@@ -373,7 +373,7 @@ struct tlb_batch {
     hipStream_t stream;
     bool own_stream;
     void* state[2];
-    int cur;  // buffer holding u_t; also the queue-counter parity of the next step
+    int cur;  // buffer holding u_t (and, without two-step launches, the queue-counter parity of the next step)
     void* wet;
     void* doms;  // DomDesc<T>[ndom]
     int2* items;
@@ -387,6 +387,7 @@ struct tlb_batch {
     int2* pair_items;
     int pair_grid;
     int single_parity;
+    bool recorded;  // a caller's graph holds steps: every run keeps the parity of the buffers and of the queues
     void* fields;
     double* staging;
     double* row_host;  // pinned host memory of one field row (lazy), null: rows go through staging
@@ -987,19 +988,33 @@ static tlb_status launch_steps(tlb_batch* b, int64_t n)
     return TLB_OK;
 }
 
+static tlb_status batch_direct(tlb_batch* b, int64_t n)
+{
+    tlb_status st = fork_groups(b);
+    if (!st) st = launch_steps(b, n);
+    if (!st) st = join_groups(b);
+    return st;
+}
+
 // nsteps steps, two to a launch: whole chains of launches from the captured graph (an even number of them,
-// from buffer 0 back to it: graph_steps steps, or twice as many), the rest directly.
+// from buffer 0 back to it: graph_steps steps, or twice as many), the rest directly.  Once a caller's graph
+// holds steps, recorded and live runs alike swap the buffers as often as single steps do, modulo two, and, as
+// all their single steps then come in the parity of the run, leave the queues' counters as a replay needs them.
 static tlb_status step_pairs(tlb_batch* b, int64_t nsteps)
 {
     tlb_status st = TLB_OK;
     const int64_t chain = b->graph_steps % 4 == 0 ? b->graph_steps : 2 * (int64_t)b->graph_steps;
-    if (chain > 0 && nsteps >= chain + (b->cur != 0 ? 2 : 0)) {
-        if (b->cur != 0) {
+    const int64_t ahead = b->cur == 0 ? 0 : b->recorded ? 1 : 2;  // steps that bring the state to buffer 0
+    if (chain > 0 && nsteps >= chain + ahead) {
+        if (ahead == 1) {
+            st = batch_direct(b, 1);
+            if (st) return st;
+        } else if (ahead == 2) {
             st = launch_pair(b, b->cur);
             if (st) return st;
             b->cur ^= 1;
-            nsteps -= 2;
         }
+        nsteps -= ahead;
         if (!b->graph_exec[0]) {
             if (b->graph[0]) (void)hipGraphDestroy(b->graph[0]);
             b->graph[0] = nullptr;
@@ -1017,28 +1032,14 @@ static tlb_status step_pairs(tlb_batch* b, int64_t nsteps)
         }
         for (; nsteps >= chain; nsteps -= chain) BHIP(hipGraphLaunch(b->graph_exec[0], b->stream));
     }
-    // a recorded run swaps the buffers as often as single steps do, modulo two: where an odd number of pairs
-    // would not, the last of them runs as single steps
-    const int64_t singles = nsteps % 2 + (nsteps % 4 >= 2 && capturing(b->stream) ? 2 : 0);
+    // where an odd number of pairs would not keep the parity, the last of them runs as single steps
+    const int64_t singles = nsteps % 2 + (nsteps % 4 >= 2 && b->recorded ? 2 : 0);
     for (; nsteps > singles; nsteps -= 2) {
         st = launch_pair(b, b->cur);
         if (st) return st;
         b->cur ^= 1;
     }
-    if (nsteps > 0) {
-        st = fork_groups(b);
-        if (!st) st = launch_steps(b, nsteps);
-        if (!st) st = join_groups(b);
-    }
-    return st;
-}
-
-static tlb_status batch_direct(tlb_batch* b, int64_t n)
-{
-    tlb_status st = fork_groups(b);
-    if (!st) st = launch_steps(b, n);
-    if (!st) st = join_groups(b);
-    return st;
+    return nsteps > 0 ? batch_direct(b, nsteps) : TLB_OK;
 }
 
 extern "C" tlb_status tlb_batch_step(tlb_batch* b, int64_t nsteps)
@@ -1047,6 +1048,7 @@ extern "C" tlb_status tlb_batch_step(tlb_batch* b, int64_t nsteps)
     if (!b->ready) return TLB_ESTATE;
     int64_t left = nsteps;
     tlb_status st = TLB_OK;
+    if (!b->recorded && capturing(b->stream)) b->recorded = true;
     if (b->pairs) {
         st = step_pairs(b, nsteps);
         if (!st) b->step += nsteps;

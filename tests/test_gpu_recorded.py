@@ -63,3 +63,30 @@ def test_live_runs_between_replays_of_recorded_steps(torch, size, prec):
             s.step(n)
         assert np.array_equal(a.field("C2"), s.field("C2")), live
         assert np.array_equal(a.all_populations(), s.all_populations()), live
+
+
+@pytest.mark.parametrize("chain", [0, 6, 8])
+@pytest.mark.parametrize("prec", [0, 1], ids=["f32", "f64"])
+def test_live_runs_between_replays_of_recorded_batch_steps(torch, prec, chain):
+    """Also odd runs, whose single steps take items from queues that a replay has to find full, and the batch's own
+    chains of launches, which start from buffer 0."""
+    from paper_1511_02155_amd import tlb
+
+    stream = torch.cuda.Stream()
+    ps = [tlb.make_params(0, nx, ny, prec=prec) for nx, ny in ((40, 30), (130, 75), (64, 64))]
+    b, sims = tlb.Batch(ps, stream=stream.cuda_stream), [tlb.Sim(p) for p in ps]
+    for d, s in enumerate(sims):
+        C = 1.0 / 3.0 + np.random.default_rng(d).uniform(-0.05, 0.05, (3, s.N))
+        b.init_equilibrium(d, C)
+        s.set_launch(**s.launch())
+        s.init_equilibrium(C)
+    b.set_graph(chain)
+    graphs = [(n, _record(torch, stream, lambda: b.step(n))) for n in (2, 4)]
+    for live in ((), (2,), (4,), (6,), (3, 1), (10,), (1, 17), (5, 3, 2), (24,)):
+        for n in live:
+            b.step(n)
+        for n, g in graphs:
+            _replay(torch, stream, g)
+        for d, s in enumerate(sims):
+            s.step(sum(live) + 6)
+            assert np.array_equal(b.all_populations(d), s.all_populations()), (live, d)
