@@ -55,8 +55,15 @@ struct tlb_sim {
     int64_t graph_steps;      // steps per captured chain (even), 0: every step launched directly
     hipGraph_t graph;         // the chain from buffer 0, captured on first use
     hipGraphExec_t graph_exec;
-    bool recorded;            // a caller's graph holds steps: every run keeps the buffers' parity (launch_steps)
+    bool recorded;            // a caller's graph reads or writes the state: every run keeps the buffers' parity (launch_steps)
 };
+
+// Before work on the state buffers is enqueued that a caller's capture may be recording: its graph keeps their
+// addresses.
+static void note_capture(tlb_sim* s)
+{
+    if (!s->recorded && capturing(s->stream)) s->recorded = true;
+}
 
 // Drop the captured chain of steps (its launches hold the parameters and launch shape of capture time).
 static void drop_graph(tlb_sim* s)
@@ -561,6 +568,7 @@ extern "C" tlb_status tlb_init_equilibrium(tlb_sim* s, const double* C, const do
 extern "C" tlb_status tlb_init_equilibrium_dev(tlb_sim* s, const void* C, const void* u)
 {
     if (!s || !C) return TLB_EINVAL;
+    note_capture(s);
     if (s->p.prec == TLB_F32) return init_impl<float, float>(s, (const float*)C, (const float*)u);
     return init_impl<double, double>(s, (const double*)C, (const double*)u);
 }
@@ -631,7 +639,7 @@ enum class Way { one, pair, four, tile };
 // of one buffer descriptor.  parity: in as many launches as steps, modulo two, so that an even run ends in
 // the buffer it started from.  A recorded run needs that to go on, replayed, from where its last replay ended;
 // and so does every later run, recorded or not, so that the next replay finds the state in the buffer that the
-// recorded launches read.
+// recorded launches read.  The same holds for a readout, a copy or an initialisation that a caller recorded.
 template <typename T>
 static tlb_status launch_steps(tlb_sim* s, int64_t n, bool parity)
 {
@@ -718,7 +726,7 @@ template <typename T>
 static tlb_status run_steps(tlb_sim* s, int64_t n)
 {
     const int64_t G = s->graph_steps;
-    if (!s->recorded && capturing(s->stream)) s->recorded = true;
+    note_capture(s);
     if (G > 0 && n >= G + (s->cur != 0 ? 1 : 0)) {
         if (s->cur != 0) {
             tlb_status st = launch_steps<T>(s, 1, false);
@@ -798,6 +806,7 @@ extern "C" tlb_status tlb_stream_only(tlb_sim* s, int64_t nsteps)
 {
     if (!s || nsteps < 0) return TLB_EINVAL;
     if (!s->ready) return TLB_ESTATE;
+    note_capture(s);
     return s->p.prec == TLB_F32 ? stream_impl<float>(s, nsteps) : stream_impl<double>(s, nsteps);
 }
 
@@ -904,6 +913,7 @@ extern "C" tlb_status tlb_get_field_dev(tlb_sim* s, int which, void* out)
 {
     if (!s || !out || field_row(s->nc, which) < 0) return TLB_EINVAL;
     if (!s->ready) return TLB_ESTATE;
+    note_capture(s);
     if (s->p.prec == TLB_F32) return field_impl<float, float>(s, which, (float*)out);
     return field_impl<double, double>(s, which, (double*)out);
 }
@@ -930,6 +940,7 @@ extern "C" tlb_status tlb_get_populations_dev(tlb_sim* s, int species, void* out
 {
     if (!s || !out || species < 0 || species >= s->nc) return TLB_EINVAL;
     if (!s->ready) return TLB_ESTATE;
+    note_capture(s);
     const AuxGeom g = geom(s);
     hipError_t e = (s->p.prec == TLB_F32)
                        ? launch_get_pops<float, float>(g, (const float*)s->state[s->cur], species, (float*)out, s->stream)
@@ -959,6 +970,7 @@ extern "C" tlb_status tlb_set_populations(tlb_sim* s, int species, const double*
 extern "C" tlb_status tlb_set_populations_dev(tlb_sim* s, int species, const void* in)
 {
     if (!s || !in || species < 0 || species >= s->nc) return TLB_EINVAL;
+    note_capture(s);
     const AuxGeom g = geom(s);
     hipError_t e = (s->p.prec == TLB_F32)
                        ? launch_set_pops<float, float>(g, (const float*)in, species, (float*)s->state[s->cur], s->stream)
@@ -1034,6 +1046,7 @@ extern "C" tlb_status tlb_save_state_dev(tlb_sim* s, void* dst)
 {
     if (!s || !dst) return TLB_EINVAL;
     if (!s->ready) return TLB_ESTATE;
+    note_capture(s);
     HIPCHK(hipMemcpyAsync(dst, s->state[s->cur], (size_t)tlb_state_bytes(s), hipMemcpyDeviceToDevice, s->stream));
     return TLB_OK;
 }
@@ -1041,6 +1054,7 @@ extern "C" tlb_status tlb_save_state_dev(tlb_sim* s, void* dst)
 extern "C" tlb_status tlb_load_state_dev(tlb_sim* s, const void* src, int64_t step)
 {
     if (!s || !src || step < 0) return TLB_EINVAL;
+    note_capture(s);
     HIPCHK(hipMemcpyAsync(s->state[s->cur], src, (size_t)tlb_state_bytes(s), hipMemcpyDeviceToDevice, s->stream));
     s->step = step;
     s->ready = true;
@@ -1372,6 +1386,7 @@ extern "C" tlb_status tlb_forward_checkpointed(tlb_sim* s, int64_t nsteps, int64
 {
     if (!s || !ckpt || nsteps < 1 || every < 1) return TLB_EINVAL;
     if (!s->ready) return TLB_ESTATE;
+    note_capture(s);
     const size_t sb = (size_t)tlb_state_bytes(s);
     for (int64_t t = 0; t < nsteps; t += every) {
         HIPCHK(hipMemcpyAsync((char*)ckpt + sb * (size_t)(t / every), s->state[s->cur], sb, hipMemcpyDeviceToDevice,

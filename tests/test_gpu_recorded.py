@@ -90,3 +90,48 @@ def test_live_runs_between_replays_of_recorded_batch_steps(torch, prec, chain):
         for d, s in enumerate(sims):
             s.step(sum(live) + 6)
             assert np.array_equal(b.all_populations(d), s.all_populations()), (live, d)
+
+
+@pytest.mark.parametrize("size", SIZES, ids=lambda s: "%dx%d" % s)
+def test_live_runs_between_replays_of_recorded_readouts(torch, size):
+    """The state's buffers are also in the graph of a readout, a copy out of or into the state, or an
+    initialisation, whether or not any step was recorded."""
+    from paper_1511_02155_amd import tlb
+
+    nx, ny = size
+    for what in ("field", "populations", "save", "load", "set", "init"):
+        stream, a, s, C = _sims(torch, tlb, nx, ny, 1)
+        n = dict(field=nx * ny, populations=9 * nx * ny, set=9 * nx * ny, init=3 * nx * ny).get(what, 27 * nx * ny)
+        t = torch.empty(n, dtype=torch.float64, device="cuda")
+        if what == "init":
+            t.copy_(torch.as_tensor(C).reshape(-1))
+        else:
+            tlb.check(tlb.tlb_save_state_dev(a.handle, t.data_ptr()) if what == "load" else
+                      tlb.tlb_get_populations_dev(a.handle, 1, t.data_ptr()) if what != "field" else 0)
+            a.synchronize()
+        start = t.cpu().numpy().copy()
+        call = dict(field=lambda: tlb.tlb_get_field_dev(a.handle, 1, t.data_ptr()),
+                    populations=lambda: tlb.tlb_get_populations_dev(a.handle, 1, t.data_ptr()),
+                    save=lambda: tlb.tlb_save_state_dev(a.handle, t.data_ptr()),
+                    load=lambda: tlb.tlb_load_state_dev(a.handle, t.data_ptr(), 0),
+                    set=lambda: tlb.tlb_set_populations_dev(a.handle, 1, t.data_ptr()),
+                    init=lambda: tlb.tlb_init_equilibrium_dev(a.handle, t.data_ptr(), None))[what]
+        torch.cuda.synchronize()
+        g = _record(torch, stream, lambda: tlb.check(call()))
+        for n in (2, 4, 10):
+            a.step(n)
+            s.step(n)
+            _replay(torch, stream, g)
+            got = t.cpu().numpy()
+            if what == "field":
+                assert np.array_equal(got, s.field("C2")), n
+            elif what == "populations":
+                assert np.array_equal(got, s.populations(1).reshape(-1)), n
+            elif what == "save":
+                assert np.array_equal(got.view(np.uint8), s.save_state()[0]), n
+            elif what == "set":
+                assert np.array_equal(a.populations(1).reshape(-1), start), n
+                s.set_populations(1, start)
+            else:  # back at the initial state
+                s.init_equilibrium(C)
+                assert np.array_equal(a.all_populations(), s.all_populations()), (what, n)
