@@ -687,11 +687,12 @@ static tlb_status launch_steps(tlb_sim* s, int64_t n, bool parity)
         a.src = (const T*)s->state[s->cur];
         a.dst = (T*)s->state[s->cur ^ 1];
         a.flip = s->cur;  // every other launch sweeps each chunk the other way
-        s->cur ^= 1;
-        return w == Way::pair   ? launch_pair2d<T>(a, 2, mrt, s->nc, s->stream)
-               : w == Way::four ? launch_pair2d<T>(a, 4, mrt, s->nc, s->stream)
-               : w == Way::tile ? launch_tile2d<T>(a, shape, mrt, s->nc, s->stream)
-                                : launch_one<T>(s, a);
+        const hipError_t e = w == Way::pair   ? launch_pair2d<T>(a, 2, mrt, s->nc, s->stream)
+                             : w == Way::four ? launch_pair2d<T>(a, 4, mrt, s->nc, s->stream)
+                             : w == Way::tile ? launch_tile2d<T>(a, shape, mrt, s->nc, s->stream)
+                                              : launch_one<T>(s, a);
+        if (e == hipSuccess) s->cur ^= 1;  // a launch that failed leaves the state where it is
+        return e;
     };
     int64_t many = n / steps, twos = 0, ones = n % steps;
     if (ones >= 2) {  // left over by launches of three or four

@@ -1,0 +1,27 @@
+"""Host code of the library over a stand-in HIP runtime (standin.py): which kernels a call launches with which
+buffers, and what a call that fails leaves behind.  Nothing is computed."""
+import pytest
+
+import standin
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("standin")
+    return lambda body, **env: standin.run(folder, body, env)
+
+
+def test_a_failed_launch_leaves_the_state_in_its_buffer(run):
+    """Of every kind of launch: the next step reads the buffer that the last successful one wrote."""
+    run("""
+for size, prec, n in (((64, 64, 1), 1, 3), ((512, 512, 1), 0, 2), ((1045, 800, 1), 1, 4), ((64, 64, 1), 1, 1), ((20, 13, 9), 0, 1)):
+    s = tlb.Sim(tlb.make_params(int(size[2] > 1), *size, prec=prec))
+    s.init_equilibrium(np.zeros((3, s.N)))
+    s.step(n)
+    wrote = buffers()[-1][1]
+    hip.standin_fail_launch(0)
+    assert tlb.tlb_step(s.handle, n) == tlb.TLB_EHIP
+    assert buffers() == []
+    s.step(n)
+    assert buffers()[0][0] == wrote, (size, n)
+""")
