@@ -1105,6 +1105,7 @@ extern "C" tlb_status tlb_batch_set_launch(tlb_batch* b, const tlb_launch* l)
     BHIP(sync_groups(b));
     const tlb_launch old = b->launch;
     const int old_groups = b->groups;
+    const bool old_pairs = b->pairs;
     b->launch = *l;
     b->groups = std::max(1, std::min(l->height, b->ndom));
     b->launch.height = b->groups;
@@ -1113,7 +1114,9 @@ extern "C" tlb_status tlb_batch_set_launch(tlb_batch* b, const tlb_launch* l)
     if (st) {  // keep the batch steppable in its previous shape
         b->launch = old;
         b->groups = old_groups;
+        b->pairs = old_pairs;
         (void)rebuild(b);
+        (void)hipGetLastError();  // returned here: the check after the next launch must not find it
     }
     return st;
 }
