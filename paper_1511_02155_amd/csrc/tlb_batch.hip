@@ -1221,9 +1221,10 @@ static std::string batch_signature(const tlb_batch* b)
     return buf;
 }
 
-// Cache lines: key width chunk variant groups (lines with fewer fields are skipped).
-// two: whether two steps per launch were faster than the shape (a last word on the line)
-static bool cache_lookup(const char* path, const std::string& key, tlb_launch* l, bool* two)
+// Cache lines: key width chunk variant groups (lines with fewer fields are skipped) and a last word: whether two
+// steps per launch were faster than the shape (1: "two", 0: "one"; -1: a line without it, written before two-step
+// launches were timed).
+static bool cache_lookup(const char* path, const std::string& key, tlb_launch* l, int* two)
 {
     FILE* f = fopen(path, "r");
     if (!f) return false;
@@ -1232,7 +1233,7 @@ static bool cache_lookup(const char* path, const std::string& key, tlb_launch* l
     bool found = false;
     while (fgets(line, sizeof(line), f))
         if ((n = sscanf(line, "%127s %d %d %d %d %7s", k, &w, &c, &v, &g, word)) >= 5 && key == k) {
-            *two = n == 6 && !strcmp(word, "two");
+            *two = n < 6 ? -1 : !strcmp(word, "two") ? 1 : !strcmp(word, "one") ? 0 : -1;
             l->width = w;
             l->height = g;
             l->chunk = c;
@@ -1250,11 +1251,12 @@ extern "C" tlb_status tlb_batch_autotune(tlb_batch* b, int32_t trial_steps, tlb_
     const char* cache = getenv("TLB_TUNE_CACHE");
     const std::string key = batch_signature(b);
     tlb_launch best;
-    bool two = false;
-    if (cache && cache_lookup(cache, key, &best, &two)) {
+    int two = -1;
+    const bool known = cache && cache_lookup(cache, key, &best, &two);
+    if (known && two >= 0) {
         tlb_status st = tlb_batch_set_launch(b, &best);
         if (st) return st;
-        b->pairs = two;
+        b->pairs = two != 0;
         if (chosen) *chosen = best;
         return TLB_OK;
     }
@@ -1270,7 +1272,7 @@ extern "C" tlb_status tlb_batch_autotune(tlb_batch* b, int32_t trial_steps, tlb_
     BHIP(hipEventCreate(&e1));
     BHIP(hipMemcpyAsync(save, b->state[cur0], bytes, hipMemcpyDeviceToDevice, b->stream));
     float best_ms = 1e30f;
-    best = b->launch;
+    if (!known) best = b->launch;
     const int widths[3] = {64, 128, 256};
     const int chunks[4] = {8, 16, 32, 64};
     tlb_status st = TLB_OK;
@@ -1295,15 +1297,20 @@ extern "C" tlb_status tlb_batch_autotune(tlb_batch* b, int32_t trial_steps, tlb_
     // one, two and four times its rows (with several groups the drain of one launch is covered by the
     // others, so longer items, with fewer halo rows, can pay), with four times the steps (these
     // differ by a few percent)
-    for (int wi = 0; wi < 3 && !st; ++wi)
-        for (int ci = 0; ci < 4 && !st; ++ci)
-            for (int v = 0; v < 3 && !st; ++v) trial(tlb_launch{widths[wi], 1, chunks[ci], v}, trial_steps);
-    const tlb_launch one = best;
-    best_ms = 1e30f;
-    margin = 0.995f;  // fewer groups and shorter items first; a later one must be faster by more than 0.5%
-    for (int g = 1; g <= std::min(kMaxGroups, b->ndom) && !st; ++g)
-        for (int f = 1; f <= 4 && !st; f *= 2)
-            if ((int64_t)one.chunk * f <= 65535) trial(tlb_launch{one.width, g, one.chunk * f, one.variant}, 4 * trial_steps);
+    if (known) {  // the shape is, but not whether two steps per launch are faster
+        trial(tlb_launch{best}, 4 * trial_steps);
+    } else {
+        for (int wi = 0; wi < 3 && !st; ++wi)
+            for (int ci = 0; ci < 4 && !st; ++ci)
+                for (int v = 0; v < 3 && !st; ++v) trial(tlb_launch{widths[wi], 1, chunks[ci], v}, trial_steps);
+        const tlb_launch one = best;
+        best_ms = 1e30f;
+        margin = 0.995f;  // fewer groups and shorter items first; a later one must be faster by more than 0.5%
+        for (int g = 1; g <= std::min(kMaxGroups, b->ndom) && !st; ++g)
+            for (int f = 1; f <= 4 && !st; f *= 2)
+                if ((int64_t)one.chunk * f <= 65535)
+                    trial(tlb_launch{one.width, g, one.chunk * f, one.variant}, 4 * trial_steps);
+    }
     // two steps per launch against the fastest of them, over the same steps
     bool pairs = false;
     if (!st) {
@@ -1331,8 +1338,8 @@ extern "C" tlb_status tlb_batch_autotune(tlb_batch* b, int32_t trial_steps, tlb_
     if (cache) {
         FILE* f = fopen(cache, "a");
         if (f) {
-            fprintf(f, "%s %d %d %d %d%s\n", key.c_str(), best.width, best.chunk, best.variant, best.height,
-                    pairs ? " two" : "");
+            fprintf(f, "%s %d %d %d %d %s\n", key.c_str(), best.width, best.chunk, best.variant, best.height,
+                    pairs ? "two" : "one");
             fclose(f);
         }
     }

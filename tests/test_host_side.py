@@ -56,3 +56,38 @@ for chain in (0, 6):
     for d in (0, 1):
         b.init_equilibrium(d, np.zeros((3, ps[d].nx * ps[d].ny)))
 """)
+
+
+def test_tuner_file_says_whether_two_steps_share_a_launch(run, tmp_path):
+    """Lines of both words are taken as they are; one without a word (written before two-step launches were timed)
+    keeps its shape, has the two ways timed, and is followed by a line that says which was faster."""
+    out = run("""
+def tuned(text=None):
+    if text is not None:
+        open(path, "w").write(text)
+    b = tlb.Batch([tlb.make_params(0, nx, ny) for nx, ny in ((40, 30), (130, 75))])
+    for d in (0, 1):
+        b.init_equilibrium(d, np.zeros((3, b._N(d))))
+    b.step(1)  # the state is in buffer 1
+    kernels()
+    shape = b.autotune(2)
+    timed = len(kernels())
+    b.step(4)
+    used = {k.split("<")[0] for k in kernels()}
+    return shape, timed, used, open(path).read().splitlines()
+
+import os
+path = os.environ["TLB_TUNE_CACHE"]
+hip.standin_cost(b"k_batch2d", 1.0)
+for pair_ms, word, kernel in ((1.0, "two", "k_batch_pair2d"), (3.0, "one", "k_batch2d")):
+    hip.standin_cost(b"k_batch_pair2d", pair_ms)
+    shape, timed, used, lines = tuned("")
+    assert timed > 0 and used == {kernel} and len(lines) == 1 and lines[0].endswith(" " + word), (used, lines)
+    bare = lines[0].rsplit(" ", 1)[0]
+    for w, k in (("two", "k_batch_pair2d"), ("one", "k_batch2d")):
+        assert tuned(bare + " " + w + chr(10)) == (shape, 0, {k}, [bare + " " + w])
+    old = tuned(bare + chr(10))
+    assert old[0] == shape and 0 < old[1] < 60 and old[2] == {kernel} and old[3] == [bare, bare + " " + word], old
+    assert tuned()[1:] == (0, {kernel}, [bare, bare + " " + word])
+""", TLB_TUNE_CACHE=str(tmp_path / "tune.txt"))
+    assert out == ""
