@@ -271,19 +271,28 @@ static void default_launch(tlb_sim* s)
             }
             return better;
         };
+        // A lattice of at most 32 columns leaves half the lanes of 64 x 4 tiles idle and gains nothing from their
+        // rows: it takes 32 x 8 (18 x 62 x 48 FP32, four components, 23.7 us per step against 29.4; 5 x 8 x 4 FP64,
+        // five components, 32.1 against 42.2).
         double best = 1e300;
         for (int bx : {64, 32})
-            if (shape(bx, 256 / bx, best, s->launch.chunk)) {
+            if ((bx == 32 || p.nx > 32) && shape(bx, 256 / bx, best, s->launch.chunk)) {
                 s->launch.width = bx;
                 s->launch.height = 256 / bx;
             }
-        // Tiles of run-time size, whose rows divide the lattice's, where they promise 8% and more (FP64
+        // Tiles of run-time size, ceil(nx / k) columns wide (the last of a row may be narrower), where they
+        // promise 8% and more (FP64
         // 11%; 17 x 121 x 26 FP64 in 17 x 15 lost 9% where the rule promised 8): 70 x 50 x 45 FP64 50 us
         // per step in 70 x 3 tiles, 58 in 64 x 4; 67 x 74 x 89 FP32 56 in 67 x 3, 70 in 64 x 4;
-        // 42 x 148 x 106 FP32, several relaxation times, 99 in 42 x 6, 130 in 64 x 4.
+        // 42 x 148 x 106 FP32, several relaxation times, 99 in 42 x 6, 130 in 64 x 4.  Not where 64 x 4 tiles
+        // already take one plane each and all run at once: a step is then an item's latency, which another width
+        // does not shorten (236 x 4 x 3 FP32 11.8 us per step in 64 x 4, 13.3 in 118 x 2; 214 x 14 x 7 of five
+        // components 21.7 and 24.2 in 107 x 2).
         s->tile_bx = 0;
         best *= p.prec == TLB_F32 ? 0.92 : 0.89;
-        for (int k = 1; (p.nx + k - 1) / k >= 12; ++k) {
+        const bool unfilled = s->launch.width == 64 && s->launch.chunk == 1 &&
+                              (int64_t)((p.nx + 63) / 64) * ((p.ny + 3) / 4) * p.nz <= slots;
+        for (int k = 1; !unfilled && (p.nx + k - 1) / k >= 12; ++k) {
             const int bx = (p.nx + k - 1) / k;
             if (bx > kTileWide) continue;
             for (int by = std::min(256 / bx, p.ny); by >= 2; --by) {

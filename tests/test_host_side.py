@@ -91,3 +91,23 @@ for pair_ms, word, kernel in ((1.0, "two", "k_batch_pair2d"), (3.0, "one", "k_ba
     assert tuned()[1:] == (0, {kernel}, [bare, bare + " " + word])
 """, TLB_TUNE_CACHE=str(tmp_path / "tune.txt"))
     assert out == ""
+
+
+def test_tiles_of_small_and_narrow_3d_lattices(run):
+    """The default tile: 32 x 8 for at most 32 columns, 64 x 4 where the chip holds all its one-plane items at once,
+    and of run-time size (0 x 0 in the kernel's name) where these fit badly, in one column of tiles and in several,
+    the last of them narrower."""
+    run("""
+tiles = {(3, 3, 3): (32, 8), (5, 8, 4): (32, 8), (20, 20, 20): (32, 8), (32, 5, 90): (32, 8), (18, 62, 48): (32, 8),
+         (236, 4, 3): (64, 4), (98, 14, 11): (64, 4), (33, 9, 4): (64, 4),
+         (70, 50, 45): (0, 0), (99, 29, 21): (0, 0), (133, 33, 127): (0, 0), (164, 63, 24): (0, 0), (132, 141, 17): (0, 0)}
+for size, tile in tiles.items():
+    for prec in (tlb.TLB_F32, tlb.TLB_F64):
+        s = tlb.Sim(tlb.make_params(1, *size, prec=prec))
+        s.init_equilibrium(np.zeros((3, s.N)))
+        kernels()
+        s.step(1)
+        name, = kernels()
+        assert name.startswith("k_step3d<%s, %d, %d, " % (("float", "double")[prec], *tile)), (size, prec, name)
+        s.close()
+""")
