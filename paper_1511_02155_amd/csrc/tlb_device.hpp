@@ -426,7 +426,11 @@ __device__ __forceinline__ void collide_core(const Phys<T>& P, const Moments<T, 
     // Directions come in pairs e_j = -e_i with the same weights (w_i and the second-order w_i^ab are
     // even in e), so an equilibrium splits into a part even in e, shared by the pair, and an odd part
     // of opposite signs: U_i = Ue + Uo, U_j = Ue - Uo with Uo = 3 e_i.v, Ue = 9/2 (e_i.v)^2 - 3/2 v^2.
-    // sf, sg, sk: half the sums of the equilibria over i > 0.
+    // sf, sg, sk: half the sums of the equilibria over i > 0.  OddOnce: the odd part is formed once per pair
+    // and added; w rho, w phi and w psi_l, which the fused form holds over all directions, would cost D3Q19 of four
+    // and five components in FP64 its last registers (100 x 96 x 90, five components: 615 us per step in 64 x 4
+    // tiles and 652 in 32 x 8, with the fused form 674 and 770).
+    constexpr bool OddOnce = L::D == 3 && NC > 3 && sizeof(T) == 8;
 #pragma unroll
     for (int i = 1; i < L::Q; ++i) {
         const int o = L::opp[i];
@@ -439,13 +443,13 @@ __device__ __forceinline__ void collide_core(const Phys<T>& P, const Moments<T, 
         if (L::D == 3) G = fmad(T(3 * wdiag<L>(i, 2)), Tzz, G);
         if (woff<L>(i, 1, 2) != 0.0) G = fmad(T(3 * woff<L>(i, 1, 2)), Tyz, G);
         if (woff<L>(i, 2, 0) != 0.0) G = fmad(T(3 * woff<L>(i, 2, 0)), Tzx, G);
-        const T fe = fmad(w, fmad(rho, Ue, A), G), fo = w * rho;
-        const T ge = w * fmad(phi, Ue, Bp), go = w * phi;
+        const T fe = fmad(w, fmad(rho, Ue, A), G), fo = OddOnce ? w * rho * Uo : w * rho;
+        const T ge = w * fmad(phi, Ue, Bp), go = OddOnce ? w * phi * Uo : w * phi;
         T ke[NK], ko[NK];
 #pragma unroll
         for (int l = 0; l < NK; ++l) {
             ke[l] = w * fmad(psi[l], Ue, Bk[l]);
-            ko[l] = w * psi[l];
+            ko[l] = OddOnce ? w * psi[l] * Uo : w * psi[l];
         }
         sf += fe;
         sg += ge;
@@ -455,7 +459,8 @@ __device__ __forceinline__ void collide_core(const Phys<T>& P, const Moments<T, 
         for (int h = 0; h < 2; ++h) {
             const int d = h == 0 ? i : o;
             const T U = h == 0 ? Uo : -Uo;
-            const T feq = fmad(fo, U, fe), geq = fmad(go, U, ge);
+            auto eq = [&](T even, T odd) { return !OddOnce ? fmad(odd, U, even) : h == 0 ? even + odd : even - odd; };
+            const T feq = eq(fe, fo), geq = eq(ge, go);
             const T fi = ld(0, d), gi = ld(1, d);
             T ki[NK];
 #pragma unroll
@@ -467,7 +472,7 @@ __device__ __forceinline__ void collide_core(const Phys<T>& P, const Moments<T, 
             }
             st(1, d, fmad(wg, geq - gi, gi));
 #pragma unroll
-            for (int l = 0; l < NK; ++l) st(2 + l, d, fmad(wk, fmad(ko[l], U, ke[l]) - ki[l], ki[l]));
+            for (int l = 0; l < NK; ++l) st(2 + l, d, fmad(wk, eq(ke[l], ko[l]) - ki[l], ki[l]));
         }
         if constexpr (MRT) {
             // the energy and stress coefficients are even in e: the pair enters its moments as a sum
