@@ -660,12 +660,15 @@ static tlb_status launch_steps(tlb_sim* s, int64_t n, bool parity)
     Way two = Way::tile;
     if (n > 1 && s->p.lattice == TLB_D2Q9 && !s->launch_set && tlb_state_bytes(s) <= (int64_t)0xFFFFFF00) {
         // Times per step in us.  The strip kernel's items of several rows are never the fastest; with one row
-        // each, a step takes about 7.0 us and 1.6 ns more per wavefront (four and five components 8.7 us and
-        // 1.5 ns up to 600 wavefronts, 12.5 us beyond).
+        // each, a step takes about 7.0 us and 1.6 ns more per wavefront; with four and five components 8.7 us and
+        // 1.5 ns up to 600 wavefronts, in FP32 9.4 us and 0.2 us per strip up to the 1024 that the chip holds, and
+        // 12.5 us beyond (1496 x 41 FP32 of five components, 984 wavefronts, 10.5 us, 12.4 in tiles).
         const double waves = (double)one.nitems * (s->launch.width / 64);
-        double best = s->launch.chunk > 1 ? 1e300
-                      : s->nc > 3         ? (waves <= 600.0 ? 8.7 + 0.0015 * waves : 12.5)
-                                          : 7.0 + 0.0016 * waves;
+        double best = s->launch.chunk > 1                       ? 1e300
+                      : s->nc == 3                              ? 7.0 + 0.0016 * waves
+                      : waves <= 600.0                          ? 8.7 + 0.0015 * waves
+                      : s->p.prec == TLB_F32 && waves <= 1024.0 ? 9.4 + 0.2 * one.ntx
+                                                                : 12.5;
         const double tp = pair2d_shape<T>(pair, s->nc, s->cus, 2);
         if (tp < best) {
             best = tp;

@@ -111,3 +111,16 @@ for size, tile in tiles.items():
         assert name.startswith("k_step3d<%s, %d, %d, " % (("float", "double")[prec], *tile)), (size, prec, name)
         s.close()
 """)
+
+
+def test_single_steps_of_five_fp32_components(run):
+    """Lattices whose one-row items fill the chip once are stepped singly, smaller, larger and very wide ones in tiles."""
+    run("""
+for size, kernel in (((400, 60), "k_tile2d"), ((1229, 45), "k_step2d"), ((1398, 38), "k_step2d"), ((1496, 41), "k_step2d"),
+                     ((2000, 28), "k_step2d"), ((4073, 15), "k_tile2d"), ((1219, 52), "k_tile2d")):
+    s = tlb.Sim(tlb.make_params(0, *size, prec=tlb.TLB_F32, kappa=[0.01] * 5))
+    s.init_equilibrium(np.zeros((5, s.N)))
+    kernels()
+    s.step(4)
+    assert {k.split("<")[0] for k in kernels()} == {kernel}, size
+""")
