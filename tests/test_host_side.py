@@ -124,3 +124,67 @@ for size, kernel in (((400, 60), "k_tile2d"), ((1229, 45), "k_step2d"), ((1398, 
     s.step(4)
     assert {k.split("<")[0] for k in kernels()} == {kernel}, size
 """)
+
+
+def test_creation_of_a_large_batch(run):
+    """Choosing the items of the two-step launches takes no longer than a few times what laying out the single-step
+    ones does (both grow with the batch's nodes), and finds the same items as dealing out every candidate."""
+    run("""
+import time
+n = 256
+ps = (tlb.tlb_params * n)(*[tlb.make_params(0, 1024, 1024, prec=tlb.TLB_F32)] * n)
+create, shape = [], []
+for _ in range(3):
+    h = ctypes.c_void_p()
+    t0 = time.perf_counter()
+    tlb.check(tlb.tlb_batch_create(ps, n, None, ctypes.byref(h)))
+    t1 = time.perf_counter()
+    tlb.check(tlb.tlb_batch_set_launch(h, ctypes.byref(tlb.tlb_launch(64, 1, 16, 0))))
+    t2 = time.perf_counter()
+    create.append(t1 - t0)
+    shape.append(t2 - t1)
+    tlb.tlb_batch_destroy(h)
+assert min(create) < 10 * min(shape), (create, shape)
+
+# the choice by its definition: the rows that end first when every queue's items are dealt in order to its slots
+import heapq
+import random
+
+
+def grid(sizes):
+    best = None
+    order = sorted(range(len(sizes)), key=lambda d: -sizes[d][0] * sizes[d][1])
+    for target in (2, 4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40, 48, 56, 64, 80, 96, 128, 192, 256):
+        rows = [-(-ny // max(1, (ny + target // 2) // target)) for _, ny in sizes]
+        chunks = [-(-ny // r) for (_, ny), r in zip(sizes, rows)]
+        work = [-(-nx // 58) * c * (r + 7) for (nx, _), c, r in zip(sizes, chunks, rows)]
+        total, load, items = sum(work), [0] * 8, [[] for _ in range(8)]
+        for d in order:
+            ntx, c = -(-sizes[d][0] // 58), chunks[d]
+            pieces = min(c, -(-work[d] * 16 // total))
+            for j in range(pieces):
+                i0, i1 = c * j // pieces, c * (j + 1) // pieces
+                k = load.index(min(load))
+                load[k] += ntx * (i1 - i0) * (rows[d] + 7)
+                items[k] += [min(rows[d], sizes[d][1] - i * rows[d]) + 7 for i in range(i0, i1) for _ in range(ntx)]
+        end = 0
+        for q in items:
+            free = []
+            for t in q:
+                at = heapq.heappop(free) if len(free) >= 4 * 256 // 8 else 0
+                heapq.heappush(free, at + t)
+                end = max(end, at + t)
+        if best is None or end < best[0]:
+            best = end, 8 * max(map(len, items))
+    return best[1]
+
+
+R = random.Random(3)
+for n, lo, hi in ((1, 300, 900), (2, 900, 1100), (5, 3, 700), (40, 20, 60), (120, 30, 300), (300, 3, 100), (60, 100, 400)):
+    sizes = [(R.randint(lo, hi), R.randint(lo, hi)) for _ in range(n)]
+    b = tlb.Batch([tlb.make_params(0, *s) for s in sizes])
+    b.init_equilibrium(0, np.zeros((3, sizes[0][0] * sizes[0][1])))
+    hip.standin_clear()
+    b.step(2)
+    assert hip.standin_grid(0) == grid(sizes), (n, lo, hi)
+""")
