@@ -412,7 +412,9 @@ tlb_status tlb_set_wetting_dev(tlb_sim* sim, int wall, const void* h_dev);
  *     after next before the current plane is collided.  Until a shape is set,
  *     lattices these tiles fit badly are stepped in tiles of another size.
  *   chunk >= 1; chunk = 0 picks a default.  The default shape depends on the
- *   lattice size and precision.  For a given variant, results are bitwise
+ *   lattice size and precision; its width, height and variant (tlb_get_launch of a
+ *   new simulation) set with chunk = 0 also lead back to steps of several to a
+ *   launch and to tiles of another size, as before any shape was set.  For a given variant, results are bitwise
  *   identical for every shape.  The D2Q9 variants are bitwise identical to each
  *   other; the D3Q19 variants are separate kernels whose results agree to
  *   rounding (the compiler may fuse different multiply-adds).  An invalid shape

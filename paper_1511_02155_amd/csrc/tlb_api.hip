@@ -835,19 +835,21 @@ extern "C" tlb_status tlb_set_launch(tlb_sim* s, const tlb_launch* l)
     if (!s || !l) return TLB_EINVAL;
     tlb_launch v = *l;
     if (s->p.lattice == TLB_D2Q9) v.height = 1;
+    bool fixed = true;  // false: the default, asked for by its width, height and variant without a chunk
     if (v.chunk == 0) {
         tlb_launch d = s->launch;
         default_launch(s);
         v.chunk = s->launch.chunk;
+        fixed = memcmp(&v, &s->launch, sizeof(v)) != 0;
         s->launch = d;
     }
     if (!launch_valid(s, &v)) return TLB_EINVAL;
-    if (!s->launch_set || memcmp(&v, &s->launch, sizeof(v)) != 0) {
+    if (fixed != s->launch_set || memcmp(&v, &s->launch, sizeof(v)) != 0) {
         HIPCHK(hipStreamSynchronize(s->stream));
         drop_graph(s);  // the captured launches have the old shape
     }
     s->launch = v;
-    s->launch_set = true;
+    s->launch_set = fixed;
     return TLB_OK;
 }
 

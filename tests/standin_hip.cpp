@@ -121,7 +121,6 @@ int hipStreamDestroy(void* s) { return free(s), 0; }
 int hipStreamSynchronize(void*) { return 0; }
 int hipStreamWaitEvent(void*, void*, unsigned) { return 0; }
 int hipStreamIsCapturing(void*, int* st) { return *st = capturing, 0; }
-int hipThreadExchangeStreamCaptureMode(int*) { return 0; }
 int hipEventCreate(double** e) { return *e = (double*)calloc(1, sizeof(double)), 0; }
 int hipEventCreateWithFlags(double** e, unsigned) { return hipEventCreate(e); }
 int hipEventDestroy(double* e) { return free(e), 0; }

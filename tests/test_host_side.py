@@ -188,3 +188,30 @@ for n, lo, hi in ((1, 300, 900), (2, 900, 1100), (5, 3, 700), (40, 20, 60), (120
     b.step(2)
     assert hip.standin_grid(0) == grid(sizes), (n, lo, hi)
 """)
+
+
+def test_the_default_launch_can_be_asked_for_again(run):
+    """A shape set by the caller is used for every step; the default's width, height and variant without a chunk is the
+    default, with several D2Q9 steps to a launch and run-time D3Q19 tiles; a captured chain is dropped each time."""
+    run("""
+for size, prec in (((1045, 800, 1), 1), ((512, 512, 1), 0), ((64, 64, 1), 1), ((70, 50, 45), 1)):
+    s = tlb.Sim(tlb.make_params(int(size[2] > 1), *size, prec=prec))
+    s.init_equilibrium(np.zeros((3, s.N)))
+    shape = s.launch()
+    for graph in (0, 4):
+        s.set_graph(graph)
+        kernels()
+        s.step(4)
+        default = kernels()
+        s.set_launch(**shape)
+        s.step(4)
+        fixed = kernels()
+        assert len(fixed) == 4 and set(fixed) != set(default), (size, graph, fixed, default)
+        s.set_launch(**dict(shape, chunk=0))
+        s.step(4)
+        assert kernels() == default and s.launch() == shape, (size, graph)
+    s.set_launch(**dict(shape, chunk=0, variant=0 if shape["variant"] else 1))
+    s.step(4)
+    assert len(kernels()) == 4, size
+    s.close()
+""")
