@@ -241,7 +241,6 @@ static void default_launch(tlb_sim* s)
         // four components hold one wavefront per SIMD in either storage, where the prefetch of the
         // next row pays; with five it spills
         s->launch.variant = (s->nc == 4 || (f64 && s->nc == 3)) ? 1 : 0;
-        s->adj_launch = default_adj_launch(p, s->cus);
     } else {
         // The default variants hold one workgroup per compute unit, so the chip runs `slots` items at
         // once, and an item's time goes with its planes and the two it starts from (about three planes'
@@ -382,6 +381,7 @@ extern "C" tlb_status tlb_create(const tlb_params* params, void* stream, tlb_sim
         return hip_fail(e);
     }
     default_launch(s);
+    if (params->lattice == TLB_D2Q9) s->adj_launch = default_adj_launch(s->p, s->cus);
     *out = s;
     return TLB_OK;
 }

@@ -215,3 +215,13 @@ for size, prec in (((1045, 800, 1), 1), ((512, 512, 1), 0), ((64, 64, 1), 1), ((
     assert len(kernels()) == 4, size
     s.close()
 """)
+
+
+def test_a_default_chunk_leaves_the_reverse_launch_alone(run):
+    run("""
+s = tlb.Sim(tlb.make_params(0, 300, 190))
+s.set_adjoint_launch(width=128, chunk=7, variant=1, rows=2)
+mine = s.adjoint_launch()
+s.set_launch(width=64, chunk=0, variant=0)
+assert s.adjoint_launch() == mine
+""")
