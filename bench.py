@@ -49,10 +49,11 @@ def kernel_sha(kind):
     return h.hexdigest()[:16]
 
 
-def measured_traffic(workload, launch=None):
+def measured_traffic(workload, launch=None, steps_per_launch=None):
     """HBM bytes per step (read + write) of a workload's dominant kernel from the committed counter
-    summary (FETCH_SIZE and WRITE_SIZE scaled by the copy-kernel calibration), or None when there is no
-    reading, the kernel's sources changed since it was taken, or it was taken at another launch shape."""
+    summary (FETCH_SIZE and WRITE_SIZE scaled by the copy-kernel calibration) and its steps per launch, or
+    None when there is no reading, the kernel's sources changed since it was taken, or it was taken at another
+    launch shape or number of steps per launch."""
     try:
         with open(TRAFFIC_FILE) as fh:
             rec = json.load(fh)[workload]
@@ -62,7 +63,10 @@ def measured_traffic(workload, launch=None):
         return None
     if launch is not None and rec.get("launch") != launch:
         return None
-    return (rec["read_bytes_per_launch"] + rec["write_bytes_per_launch"]) / rec.get("steps_per_launch", 1)
+    n = rec.get("steps_per_launch", 1)
+    if steps_per_launch is not None and n != steps_per_launch:
+        return None
+    return (rec["read_bytes_per_launch"] + rec["write_bytes_per_launch"]) / n, n
 
 
 def _events_time(torch, stream, fn):
@@ -91,27 +95,29 @@ def run_plain(tlb, torch, w, prec, steps, warmup, launch=None):
     ms = _events_time(torch, stream, lambda: sim.step(steps))
     d = sim.diagnostics()
     N = w["nx"] * w["ny"] * w["nz"]
-    per_launch_ms = ms / steps
-    bytes_per_launch = sim.bytes_per_node() * N
+    per_step_ms = ms / steps
+    bytes_per_step = sim.bytes_per_node() * N
     # the same bytes in the same pattern and launch shape without the arithmetic (propagation alone),
     # timed after the step's state was read out
     ns = min(steps, 200)
     sim.stream_only(2)
     ms_stream = _events_time(torch, stream, lambda: sim.stream_only(ns)) / ns
+    # D2Q9 without a launch shape takes several steps per launch, in shapes of its own: the bytes it moves are
+    # below the steps' own, which achieved_GBps counts, and one step's pattern is no ceiling
+    several = w["lattice"] == 0 and not launch
     out = dict(
         ms_total=ms,
-        ms_per_step=per_launch_ms,
+        ms_per_step=per_step_ms,
         mlups=N * steps / (ms * 1e-3) / 1e6,
-        achieved_GBps=bytes_per_launch / (per_launch_ms * 1e-3) / 1e9,
+        achieved_GBps=bytes_per_step / (per_step_ms * 1e-3) / 1e9,
         bytes_per_node=sim.bytes_per_node(),
-        bytes_per_launch=bytes_per_launch,
+        bytes_per_launch=bytes_per_step,
         nodes=N,
-        launch=sim.launch(),
+        launch=None if several else sim.launch(),
+        several_steps_per_launch=several,
         steps=steps,
-        # D2Q9 without a launch shape: several steps per launch, whose bytes are below the sum of its steps'
-        # bytes that achieved_GBps counts
-        kernel="k_step3d" if w["lattice"] == 1 else ("k_step2d" if launch else "k_pair2d"),
-        pattern_ceiling_GBps=bytes_per_launch / (ms_stream * 1e-3) / 1e9,
+        kernel="k_step3d" if w["lattice"] == 1 else ("k_pair2d" if several else "k_step2d"),
+        pattern_ceiling_GBps=bytes_per_step / (ms_stream * 1e-3) / 1e9,
         mass=d["mass"],
         max_speed=d["max_speed"],
         nonfinite=d["nonfinite"],
@@ -120,12 +126,32 @@ def run_plain(tlb, torch, w, prec, steps, warmup, launch=None):
     return out
 
 
+def _tuned(b):
+    """Autotunes the batch; returns the single-step shape and whether two steps per launch were faster (the last
+    word of its line in the tuner's file: the caller's TLB_TUNE_CACHE, or one for this call)."""
+    import tempfile
+
+    with tempfile.TemporaryDirectory() as tmp:
+        mine = "TLB_TUNE_CACHE" not in os.environ
+        path = os.environ.setdefault("TLB_TUNE_CACHE", os.path.join(tmp, "tune.txt"))
+        try:
+            chosen = b.autotune(10)
+            shape = "%d %d %d %d" % (chosen["width"], chosen["chunk"], chosen["variant"], chosen["groups"])
+            with open(path) as fh:
+                lines = [ln.split(None, 1)[1].strip() for ln in fh if ln.startswith("batch-d2q9-f32-%d-" % b.ndom)]
+        finally:
+            if mine:
+                del os.environ["TLB_TUNE_CACHE"]
+    return chosen, [ln for ln in lines if ln.startswith(shape)][-1].endswith(" two")
+
+
 def run_batched(tlb, torch, steps, warmup=10, graph_steps=50):
     """The 512-domain batched workload (FP32, walls, per-domain kappa and h): autotuned launch
     shape (outside the timed region), steps replayed from captured hipGraphs.  With the domains split
     over G stream groups a step is G concurrent launches, one per group; the events on the batch's
     stream bracket all of them (the groups join it at the end of every step call), and the bytes
-    are those of a whole step."""
+    are those of a whole step.  Where the tuner finds two steps per launch faster, one launch on the batch's
+    stream advances all domains by two; its file says so."""
     doms = inputs_mod().batched_walls()
     keys = ("lattice", "nx", "ny", "nz", "walls_y", "kappa", "alpha", "tau_f", "tau_g", "tau_k", "gamma_phi",
             "gamma_psi")
@@ -136,7 +162,7 @@ def run_batched(tlb, torch, steps, warmup=10, graph_steps=50):
         b.set_wetting(i, 0, d["h"][0])
         b.set_wetting(i, 1, d["h"][1])
         b.init_equilibrium(i, d["C"])
-    chosen = b.autotune(10)
+    chosen, two = _tuned(b)
     b.set_graph(graph_steps)
     b.step(warmup)
     b.synchronize()
@@ -145,8 +171,9 @@ def run_batched(tlb, torch, steps, warmup=10, graph_steps=50):
     bytes_per_step = 216.0 * nodes
     out = dict(mlups=nodes * steps / (ms * 1e-3) / 1e6, ms_per_step=ms / steps,
                achieved_GBps=bytes_per_step / (ms / steps * 1e-3) / 1e9, domains=len(doms), nodes=nodes,
-               steps=steps, launch=chosen, graph_steps=graph_steps, bytes_per_launch=bytes_per_step,
-               launches_per_step=chosen["groups"], kernel="k_batch_pair2d or k_batch2d (the tuner's choice)")
+               steps=steps, launch=None if two else chosen, graph_steps=graph_steps, bytes_per_launch=bytes_per_step,
+               several_steps_per_launch=two, launches_per_step=0.5 if two else chosen["groups"],
+               kernel="k_batch_pair2d" if two else "k_batch2d")
     b.close()
     return out
 
@@ -388,13 +415,23 @@ def main():
     res = {}  # workload name -> measurements, the headline first
 
     def add(name, r):
+        several = r.get("several_steps_per_launch", False)
+        if several:
+            t = measured_traffic(name)
+            t = t if t and t[1] > 1 else None
+        else:
+            t = measured_traffic(name, r.get("launch"), 1)
+        r["traffic"] = t and t[0]
+        if t:
+            r["traffic_over_algorithmic"] = t[0] / r["bytes_per_launch"]
+            r["steps_per_launch"] = t[1]
+        # the share of the peak that the step's own bytes come to or, where several steps share a launch, the
+        # bytes it was measured to move
         r["frac_of_hbm"] = r["achieved_GBps"] / HBM_PEAK_GBS
-        if r.get("pattern_ceiling_GBps"):
+        if several:
+            r["frac_of_hbm"] = t and t[0] / (r["ms_per_step"] * 1e-3) / 1e9 / HBM_PEAK_GBS
+        elif r.get("pattern_ceiling_GBps"):
             r["frac_of_pattern_ceiling"] = r["achieved_GBps"] / r["pattern_ceiling_GBps"]
-        t = measured_traffic(name, r.get("launch"))
-        r["traffic"] = t
-        if t is not None:
-            r["traffic_over_algorithmic"] = t / r["bytes_per_launch"]
         res[name] = r
 
     if sel in (None, "d3q19"):
@@ -465,8 +502,7 @@ def main():
                      "kernel": head.get("kernel"), "bytes_per_launch": head["bytes_per_launch"],
                      "frac_of_copy_kernel": head["achieved_GBps"] / copy_gbps,
                      "pattern_ceiling": head.get("pattern_ceiling_GBps"),
-                     "frac_of_pattern_ceiling": (head["achieved_GBps"] / head["pattern_ceiling_GBps"]
-                                                 if head.get("pattern_ceiling_GBps") else None)},
+                     "frac_of_pattern_ceiling": head.get("frac_of_pattern_ceiling")},
         "check": {"nonfinite": head.get("nonfinite"), "mass": head.get("mass")},
     }
     if not args.no_cpu and hname == "d3q19_256cube_spinodal_f32":

@@ -220,6 +220,12 @@ tlb_status tlb_init_equilibrium(tlb_sim* sim, const double* C, const double* u);
  * eq. eqdistfbinary built from the chemical potentials and pressure tensor of
  * Sec. III and the wetting condition of Sec. II.B) followed by propagation
  * (eq. latboltPropagation) with half-way bounce-back at the walls.
+ * Steps, readouts and copies may be recorded into a caller's graph by capturing
+ * the stream.  A recorded call holds the buffer that the state is in at that time;
+ * from then on a run of an even number of steps, recorded and replayed or live,
+ * leaves the state in the buffer where it found it, so that replays and live calls
+ * may alternate as long as each replay starts where the recording did, an even
+ * number of steps apart.
  * TLB_EINVAL for nsteps < 0, TLB_ESTATE before the state is initialised,
  * TLB_ENAN from the periodic check of tlb_set_check_every. */
 tlb_status tlb_step(tlb_sim* sim, int64_t nsteps);
@@ -449,9 +455,10 @@ double tlb_bytes_per_node(const tlb_sim* sim);
  * Propagation alone: nsteps >= 0 times the pull of the fused step (with
  * half-way bounce-back, eq. latboltPropagation) and its store, with no
  * collision, in the step's work decomposition and current launch shape (the
- * D3Q19 tiles without their ring).  It moves exactly the bytes of a step in
- * exactly its access pattern, so its bandwidth is the ceiling that pattern
- * leaves the fused step.  It changes the state (to the free-streamed one) but
+ * D3Q19 tiles without their ring).  It moves exactly the bytes of a single step
+ * in exactly its access pattern, so its bandwidth is the ceiling that pattern
+ * leaves a step in the shape of tlb_get_launch (steps that share a launch move
+ * fewer bytes, and tiles of another size have a pattern of their own).  It changes the state (to the free-streamed one) but
  * not the step counter; a measurement call.  Asynchronous on the stream.
  */
 tlb_status tlb_stream_only(tlb_sim* sim, int64_t nsteps);
@@ -472,12 +479,15 @@ tlb_status tlb_device_copy(void* dst, const void* src, int64_t bytes, void* stre
  * A batch advances ndom independent D2Q9 lattices (the benchmark geometries
  * of Sec. V, e.g. sweeps over kappa_m and h_m) together.  Each domain has its
  * own tlb_params (lattice TLB_D2Q9, nx, ny <= 65535, its own walls_y, kappa,
- * alpha, tau and Gamma); every domain must use the same prec.  One time step
- * of the batch is one persistent kernel launch per stream group (one group
- * unless tlb_batch_set_launch asks for more) whose workgroups take
- * (domain, strip, row-chunk) or (domain, run of positions) work items from
- * per-XCD queues; with tlb_batch_set_graph the steps are replayed from
- * captured hipGraphs (one per group).
+ * alpha, tau and Gamma); every domain must use the same prec.  Until a launch
+ * shape is set, two time steps of the batch share one launch on the batch's
+ * stream, whose workgroups each take one (domain, strip, row-chunk) item; an odd
+ * step, and with a shape set every step, is one persistent kernel launch per
+ * stream group (one group unless tlb_batch_set_launch asks for more) whose
+ * workgroups take (domain, strip, row-chunk) or (domain, run of positions) work
+ * items from per-XCD queues.  With tlb_batch_set_graph the launches are replayed
+ * from captured hipGraphs (one per group; one in all for two-step launches).
+ * Live and recorded runs may alternate as with tlb_step.
  * A domain evolves exactly (bit for bit) as a tlb_sim with the same
  * parameters.  Domain indices run 0..ndom-1; host arrays follow the layouts
  * of the single-lattice calls for that domain's nx, ny.
@@ -516,8 +526,10 @@ tlb_status tlb_batch_diagnostics(tlb_batch* batch, int32_t dom, tlb_diag* out);
  * back into the batch's stream inside tlb_batch_step, so that one group's
  * launch fills the compute units another group's launch leaves idle as it
  * drains.  With more than one group every group runs on a stream the
- * library creates (four, together, at the default priority).  Results do
- * not depend on the shape.
+ * library creates (four, together, at the default priority).  A shape set here
+ * is used for every step, one step at a time; only tlb_batch_autotune leads back
+ * to two steps per launch, where it finds them faster.  A shape that cannot be
+ * set (TLB_ENOMEM) leaves the batch as it was.  Results do not depend on the shape.
  */
 tlb_status tlb_batch_set_launch(tlb_batch* batch, const tlb_launch* launch);
 tlb_status tlb_batch_get_launch(const tlb_batch* batch, tlb_launch* out);
@@ -526,13 +538,20 @@ tlb_status tlb_batch_get_launch(const tlb_batch* batch, tlb_launch* out);
  * (which is restored) in one stream group, then the fastest of them in 1, 2,
  * 3 and 4 groups, each with its chunk and with twice and four times its
  * chunk, for 4 * trial_steps steps each, and keep the fastest of those;
- * writes it to *chosen if not NULL.
+ * writes it to *chosen if not NULL.  Two steps per launch are timed against it
+ * over as many steps and used where they are faster (*chosen and
+ * tlb_batch_get_launch then still name the single-step shape, which odd steps take).
  * If the environment variable TLB_TUNE_CACHE names a file, a previous result
- * for the same domain sizes is taken from it, and new results are appended.
+ * for the same domain sizes is taken from it, and new results are appended: the
+ * shape and, as a last word, "two" or "one" (steps per launch).  For a line
+ * without that word only the two ways are timed, with its shape.
  */
 tlb_status tlb_batch_autotune(tlb_batch* batch, int32_t trial_steps, tlb_launch* chosen);
 /* Capture steps_per_graph (even, > 0) steps once in a hipGraph and replay it
- * inside tlb_batch_step; 0 launches every step directly (the default). */
+ * inside tlb_batch_step; 0 launches every step directly (the default).  A graph of
+ * two-step launches holds twice as many steps where steps_per_graph is no multiple
+ * of four (it starts and ends in the same buffer); shorter runs, and what is left
+ * over, are launched directly. */
 tlb_status tlb_batch_set_graph(tlb_batch* batch, int32_t steps_per_graph);
 
 #ifdef __cplusplus

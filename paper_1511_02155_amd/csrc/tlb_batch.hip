@@ -1,7 +1,8 @@
 // Batched D2Q9 ternary LB: many independent lattices of uneven size and
 // parameters advanced together.
 //
-// One time step of the whole batch is one persistent launch per stream group
+// By default two time steps of the whole batch share one launch (k_batch_pair2d).  Odd steps, and every step once a
+// launch shape is set or the tuner finds it faster, are single: one persistent launch per stream group
 // (the domains split into up to four groups of nearly equal work, each on its
 // own stream, so that one group's launch fills the compute units another's
 // leaves idle as it drains): a grid sized to
@@ -291,8 +292,10 @@ void k_batch2d(BatchArgs<T> B)
 // Two steps of the whole batch in one launch: each workgroup takes one item (a strip of a domain's columns
 // over a chunk of its rows) and runs the two-step sweep of the single lattice on it, so that two steps read
 // and write the state once.  Items are dealt to the XCDs (blocks b, b + 8, ... of queue b mod 8) whole
-// domains at a time, balanced by their rows; a queue shorter than the longest ends in empty items.
+// domains at a time, the largest in pieces of neighbouring rows, balanced by their rows (build_pairs); a queue
+// shorter than the longest ends in empty items.
 // 512 domains of 32 to 256 nodes a side, FP32: 356 us per step against 565 in tuned one-step launches.
+// In FP64 two wavefronts per SIMD (256 registers) leave 16 values in scratch memory (52 bytes per lane).
 template <typename T>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k_batch_pair2d(BatchArgs<T> B)
 {
