@@ -749,7 +749,8 @@ static tlb_status run_steps(tlb_sim* s, int64_t n)
         if (!s->graph_exec) {
             drop_graph(s);  // a graph left by a failed instantiation
             HIPCHK(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
-            tlb_status st = launch_steps<T>(s, G, true);  // recorded, not run: cur is back at 0
+            tlb_status st = launch_steps<T>(s, G, true);
+            s->cur = 0;  // recorded, not run, whether or not all of it was
             hipGraph_t g = nullptr;
             const hipError_t e = hipStreamEndCapture(s->stream, &g);
             if (st) {

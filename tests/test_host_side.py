@@ -225,3 +225,21 @@ mine = s.adjoint_launch()
 s.set_launch(width=64, chunk=0, variant=0)
 assert s.adjoint_launch() == mine
 """)
+
+
+def test_a_chain_that_cannot_be_recorded_leaves_the_state_in_its_buffer(run):
+    run("""
+for size, lattice in (((1045, 800, 1), 0), ((20, 13, 9), 1)):
+    s = tlb.Sim(tlb.make_params(lattice, *size))
+    s.init_equilibrium(np.zeros((3, s.N)))
+    s.step(1)
+    s.step(1)
+    holds = buffers()[-1][1]
+    s.set_graph(4)
+    hip.standin_fail_launch(1)
+    assert tlb.tlb_step(s.handle, 8) == tlb.TLB_EHIP
+    assert len(kernels()) == 1  # one of the chain's launches was recorded, none has run
+    s.set_graph(0)
+    s.step(1)
+    assert buffers()[0][0] == holds, size
+""")
